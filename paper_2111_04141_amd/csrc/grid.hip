@@ -83,6 +83,8 @@ __device__ inline int unit_scale(int32_t info) { return (info & 0xff) - 128; }
 struct GridParams {
     int32_t npol, nu, nv, beta;
     int32_t p_lo, p_hi;       // planes handled by this launch
+    uint32_t conj_base;       // element offset of the conjugated copy of the bank
+    uint32_t tab_bytes;       // window kernels: LDS for a plane's tap table
 };
 
 // Two 16-bit lanes of a 32-bit word (packed 16-bit integer arithmetic).
@@ -145,19 +147,36 @@ __device__ inline uint32_t next_chunk(uint32_t *queue, uint32_t *slot) {
 // contiguous share of q = ceil(S^2 / TEAM) slots, at most KMAX per lane
 // (q <= 64 KMAX); the workgroup's NW / TEAM teams take consecutive parts of
 // each chunk's records, each team with its own window.
-// Each slot keeps its cell and the term cell_v S + cell_u (W-projection;
-// separable: cell_u and cell_v) of its tap offset (bytes, modulo 2^32); a
-// record subtracts its own term, so the slot's tap offset costs one
-// subtraction per record, and only slots whose cell leaves the footprint do
-// more work.
+// Each slot keeps its cell and the term cell_v S + cell_u (separable taps
+// outside LDS: cell_u and cell_v) of its tap offset (bytes, modulo 2^32); a
+// record adds its own term, so the slot's tap offset costs one addition per
+// record, and only slots whose cell leaves the footprint do more work.
 // Work items are units: chunks of one tile over the planes of the launch's
 // group.  An item's sums go to an LDS region covering what its chunks can
 // touch, in fixed point, and from there to the grid once per item.
-// Waves per workgroup: four single-wave teams, or eight waves in teams of
-// TEAM (two such workgroups share a CU's LDS for supports up to 32, and the
-// multi-wave instances are held to four waves per SIMD: beyond 128 VGPRs the
-// eight-slot instance ran a third slower at three waves per SIMD).
-constexpr int window_waves(int team) { return team == 1 ? 4 : 8; }
+//
+// The multiply-adds run on the matrix cores: v_mfma_f32_4x4x1_16b takes four
+// visibility components as its A column (broadcast to the 16 blocks) and one
+// tap per lane as its B row, so lane l of the result holds four components of
+// cell l, the layout the slots have anyway, and every product is one fused
+// multiply-add, bit for bit what v_fma_f32 gives.  FP32 matrix and vector
+// instructions do not overlap on a SIMD (measured: their times add), but the
+// four matrix instructions of a complex tap take 43 cycles for 64 cells where
+// sixteen v_fma_f32 take 54, and the visibilities need no scalar registers.
+// The taps come from a copy of the plane's phase-major table in LDS where it
+// fits (the launch's tab_bytes) and the chunk is long enough to pay for the
+// copy: a load of 64 lanes of 4 or 8 bytes in a footprint's rotated order
+// takes the CU's L1 17 cycles, shared by four SIMDs, and LDS 5.  A separable
+// table is held as the S x S products of its phases, one load instead of two.
+// Measured on the W-projection benchmark workload (133.7M records, 8192^2),
+// against scalar-unit visibilities, v_fma_f32 and global taps: S <= 8 3.29 ->
+// 2.70 ms, S <= 16 7.01 -> 6.80 ms, S <= 32 6.53 -> 6.22 ms; separable 7 x 7,
+// 10.08M records on 2048^2: 0.714 -> 0.426 ms.
+// Waves per workgroup: eight (two such workgroups share a CU's LDS for
+// supports up to 32, and the instances with several slots per lane are held
+// to four waves per SIMD: beyond 128 VGPRs the eight-slot instance ran a
+// third slower at three waves per SIMD).
+constexpr int kWindowWaves = 8;
 // Largest support of each window instance and its LDS region: 8 planes
 // (polarisations x re/im) of int32, each plane kWindowTile + S - 1 cells
 // square at most.  The plane stride is a compile-time constant, so the eight
@@ -167,36 +186,62 @@ constexpr int window_smax(int kmax) { return kmax == 1 ? 8 : kmax == 4 ? 16 : 32
 constexpr int window_plane(int kmax) {
     return (kWindowTile + window_smax(kmax) - 1) * (kWindowTile + window_smax(kmax) - 1);
 }
-// dynamic LDS of a window instance: the region and the unit slot
-constexpr size_t window_lds(int kmax) { return sizeof(int32_t) * (8 * (size_t)window_plane(kmax) + 1); }
+// LDS words of a window instance before the tap table: the region and the
+// unit slot, rounded to 8 bytes
+constexpr int window_words(int kmax) { return 8 * window_plane(kmax) + 2; }
+constexpr size_t window_lds(int kmax) { return sizeof(int32_t) * (size_t)window_words(kmax); }
+// LDS a workgroup may take so that two share a CU's 160 KB
+constexpr size_t kWindowLds = 80 * 1024;
+// Records a chunk needs, per oversampling phase, for its plane's table to be
+// copied to LDS: the copy reads the table once through an L1 of about 32 bytes
+// a cycle, what the records would read themselves over 1 / kStagePerPhase of
+// the chunk.
+constexpr uint32_t kStagePerPhase = 16;
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// acc += a[0..3] b for every lane's b, a in lanes 4 BLOCK .. 4 BLOCK + 3
+template <int BLOCK>
+__device__ inline f32x4 mfma_col(float a, float b, f32x4 acc) {
+    return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, acc, 4, BLOCK, 0);
+}
 
 template <int KMAX, int TEAM, bool SEP, typename TapT>
-__global__ __launch_bounds__(kWave * window_waves(TEAM))
-__attribute__((amdgpu_waves_per_eu(TEAM > 1 ? 4 : 1))) void grid_window_kernel(
-    const RecMeta *__restrict__ smeta, const float4 *__restrict__ svis, float *__restrict__ grid,
+__global__ __launch_bounds__(kWave * kWindowWaves)
+__attribute__((amdgpu_waves_per_eu(4))) void grid_window_kernel(
+    const RecMeta *__restrict__ smeta, const float *__restrict__ svis, float *__restrict__ grid,
     const TapT *__restrict__ taps, const Chunk *__restrict__ chunks,
     const uint32_t *__restrict__ bucket_cfirst, const uint2 *__restrict__ units,
     const uint32_t *__restrict__ group_nunits, const PlaneLayout *__restrict__ planes,
     const int32_t *__restrict__ uinfo, uint32_t *__restrict__ queue, GridParams prm) {
-    constexpr int NW = window_waves(TEAM);
+    constexpr int NW = kWindowWaves;
     constexpr int NTEAMS = NW / TEAM;
     constexpr int PS = window_plane(KMAX);   // plane stride (cells)
     // [8][PS], plane q holding [RH][RW], then the workgroup's unit slot (the
-    // region starts at LDS address 0, so commit addresses need no base)
+    // region starts at LDS address 0, so commit addresses need no base), then
+    // the tap table
     extern __shared__ int32_t region[];
     uint32_t *const s_next = reinterpret_cast<uint32_t *>(region + 8 * PS);
+    char *const s_tab = reinterpret_cast<char *>(region + window_words(KMAX));
     constexpr uint32_t kElem = SEP ? sizeof(TapT) : 2 * sizeof(TapT);   // bytes per tap
+    constexpr uint32_t kElemLds = SEP ? sizeof(float) : kElem;          // the same in LDS
     const int wave = (int)uniform_u32(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int team = wave / TEAM, member = wave % TEAM;
     const int npol = prm.npol;
     const char *tbase = reinterpret_cast<const char *>(taps);
+    const uint32_t beta = (uint32_t)prm.beta;
+
+    // sign of the second A column: (re, im) -> (-im, re)
+    const uint32_t swap_sign = (lane & 1) ? 0u : 0x80000000u;
+    const int rot16 = ((lane + 16) & 63) << 2;
 
     // the launch covers one plane group; its work items are the group's units
     const PlaneLayout gl = planes[prm.p_lo];
     const uint32_t ubase = bucket_cfirst[gl.base];
     const uint2 *gunits = units + ubase;
     const uint32_t nunits = group_nunits[prm.p_lo];
+    int staged = -1;   // plane whose tap table is in LDS
     for (uint32_t it = next_chunk(queue, s_next); it < nunits; it = next_chunk(queue, s_next)) {
         const uint2 un = gunits[it];
         const uint32_t c0 = un.x, c1 = un.x + un.y;
@@ -242,7 +287,7 @@ __attribute__((amdgpu_waves_per_eu(TEAM > 1 ? 4 : 1))) void grid_window_kernel(
         }
         // adds a slot's sums to its cell (fixed point: rounded to the nearest
         // quantum)
-        auto commit = [&](float (&sums)[8], uint32_t cell_uv) {
+        auto commit = [&](const f32x4 &s0, const f32x4 &s1, uint32_t cell_uv) {
             const uint32_t cu_ = cell_uv & 0xffffu, cv_ = cell_uv >> 16;
             if (use_lds) {
                 // (the products are below 2^24 and the sum is the cell's
@@ -250,15 +295,17 @@ __attribute__((amdgpu_waves_per_eu(TEAM > 1 ? 4 : 1))) void grid_window_kernel(
                 int32_t *dst = reinterpret_cast<int32_t *>(reinterpret_cast<char *>(region) +
                                                            dot_uv(cell_uv, rstep, rbias));
 #pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    atomicAdd(&dst[q * PS], round_to_fixed(sums[q]));
+                for (int q = 0; q < 4; ++q) {
+                    atomicAdd(&dst[q * PS], round_to_fixed(s0[q]));
+                    atomicAdd(&dst[(q + 4) * PS], round_to_fixed(s1[q]));
+                }
             } else {
 #pragma unroll
                 for (int pol = 0; pol < 4; ++pol) {
                     if (pol < npol) {
                         float *dst = grid + 2 * (((int64_t)pol * prm.nv + cv_) * prm.nu + cu_);
-                        unsafeAtomicAdd(dst, sums[2 * pol]);
-                        unsafeAtomicAdd(dst + 1, sums[2 * pol + 1]);
+                        unsafeAtomicAdd(dst, pol < 2 ? s0[2 * pol] : s1[2 * pol - 4]);
+                        unsafeAtomicAdd(dst + 1, pol < 2 ? s0[2 * pol + 1] : s1[2 * pol - 3]);
                     }
                 }
             }
@@ -270,11 +317,31 @@ __attribute__((amdgpu_waves_per_eu(TEAM > 1 ? 4 : 1))) void grid_window_kernel(
             uint32_t tile_;
             bucket_plane_tile(gl, ch.bucket, &pc, &tile_);
             const int S = planes[pc].S;
-            // offset terms per cell step (bytes; phase-major table)
-            const uint32_t su_step = kElem;
-            const uint32_t sv_step = SEP ? kElem : (uint32_t)S * kElem;
-            // the same steps packed (u, v) for the dot product with a cell
-            const uint32_t uv_step = su_step | (sv_step << 16);
+            const uint32_t tap_off = planes[pc].tap_off;
+            const uint32_t ntap = beta * beta * (uint32_t)(S * S);   // phase-major S x S blocks
+            bool in_lds = staged == pc;
+            if (!in_lds && ch.len >= kStagePerPhase * beta * beta && ntap * kElemLds <= prm.tab_bytes) {
+                __syncthreads();   // the previous table's readers are done
+                if constexpr (SEP) {
+                    float *t = reinterpret_cast<float *>(s_tab);
+                    for (uint32_t e = threadIdx.x; e < ntap; e += NW * kWave) {
+                        const uint32_t blk = e / (uint32_t)(S * S), r = e - blk * (uint32_t)(S * S);
+                        const uint32_t j = r / (uint32_t)S, i = r - j * (uint32_t)S;
+                        const uint32_t ov = blk / beta, ou = blk - ov * beta;
+                        t[e] = TapTraits<TapT>::real(taps, ou * (uint32_t)S + i) *
+                               TapTraits<TapT>::real(taps, ov * (uint32_t)S + j);
+                    }
+                } else {
+                    const uint32_t *src = reinterpret_cast<const uint32_t *>(
+                        tbase + (size_t)tap_off * kElem);
+                    uint32_t *t = reinterpret_cast<uint32_t *>(s_tab);
+                    for (uint32_t e = threadIdx.x; e < ntap * (kElem / 4); e += NW * kWave)
+                        t[e] = src[e];
+                }
+                __syncthreads();
+                staged = pc;
+                in_lds = true;
+            }
 
             // this wave's slots: member * q + k * 64 + lane (q = ceil(S^2 / TEAM));
             // per-lane flags are bit fields (bit k = slot k).  The slot count
@@ -282,11 +349,19 @@ __attribute__((amdgpu_waves_per_eu(TEAM > 1 ? 4 : 1))) void grid_window_kernel(
             // instance of the chunk's loop.
             const int nslots = S * S;
             const int q_ = (nslots + TEAM - 1) / TEAM;
-            auto run = [&](auto kd_t) {
+            auto run = [&](auto kd_t, auto lds_t) {
                 constexpr int KD = decltype(kd_t)::value;
+                constexpr bool LDS = decltype(lds_t)::value;
+                constexpr bool SEP1D = SEP && !LDS;   // two 1-D taps multiplied per record
+                constexpr uint32_t kE = LDS ? kElemLds : kElem;
+                // offset terms per cell step (bytes; phase-major table)
+                const uint32_t su_step = kE;
+                const uint32_t sv_step = SEP1D ? kE : (uint32_t)S * kE;
+                // the same steps packed (u, v) for the dot product with a cell
+                const uint32_t uv_step = su_step | (sv_step << 16);
                 uint32_t cell[KD], lo[KD], lov[KD], suv[KD];
                 uint32_t valid_bits = 0;
-                float acc[KD][8];
+                f32x4 acc0[KD], acc1[KD];
 #pragma unroll
                 for (int k = 0; k < KD; ++k) {
                     const int j = k * kWave + lane;
@@ -302,19 +377,13 @@ __attribute__((amdgpu_waves_per_eu(TEAM > 1 ? 4 : 1))) void grid_window_kernel(
                     cell[k] = kNoCell;
                     lo[k] = 0u;
                     lov[k] = 0u;
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) acc[k][q] = 0.0f;
+                    acc0[k] = acc1[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
                 }
 
-                // window of the current footprint: slots whose cell left it commit
+                // window of the footprint at kuv: slots whose cell left it commit
                 // and take the cell congruent to them inside the new footprint
-                uint32_t prev_kuv = 0xffffffffu;
-                uint32_t ru = 0, rv = 0;   // the record's offset terms (bytes, modulo 2^32)
-                auto window_update = [&](const RecMeta m) {
-                    const uint32_t kuv = m.kuv;
-                    if (kuv == prev_kuv) return;
-                    prev_kuv = kuv;
-                    const uint32_t ku = meta_ku(m), kv = meta_kv(m);
+                auto window_update = [&](const uint32_t kuv) {
+                    const uint32_t ku = kuv & 0xffffu, kv = kuv >> 16;
                     const uint32_t kmu = ku % (uint32_t)S, kmv = kv % (uint32_t)S;
                     // (u, v) pairs in 16-bit halves: the footprint origin, its
                     // residues mod S and S itself
@@ -327,9 +396,8 @@ __attribute__((amdgpu_waves_per_eu(TEAM > 1 ? 4 : 1))) void grid_window_kernel(
                         const uint32_t d = cell[k] - kuv;
                         if (max(d & 0xffffu, d >> 16) >= (uint32_t)S) {
                             if (((valid_bits >> k) & 1u) && cell[k] != kNoCell)
-                                commit(acc[k], cell[k]);
-#pragma unroll
-                            for (int q = 0; q < 8; ++q) acc[k][q] = 0.0f;
+                                commit(acc0[k], acc1[k], cell[k]);
+                            acc0[k] = acc1[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
                             // the cell congruent to the slot in the footprint:
                             // origin + (slot - origin mod S) mod S, per half; a
                             // negative difference wraps above 2^15, and adding S
@@ -340,7 +408,7 @@ __attribute__((amdgpu_waves_per_eu(TEAM > 1 ? 4 : 1))) void grid_window_kernel(
                             cell[k] = as_u32(cc);
                             // cells < 2^16 and steps < 2^10: the products
                             // and their sum are exact
-                            if constexpr (SEP) {
+                            if constexpr (SEP1D) {
                                 lo[k] = dot_uv(cell[k], su_step, 0u);
                                 lov[k] = dot_uv(cell[k], sv_step << 16, 0u);
                             } else {
@@ -348,119 +416,220 @@ __attribute__((amdgpu_waves_per_eu(TEAM > 1 ? 4 : 1))) void grid_window_kernel(
                             }
                         }
                     }
-                    if constexpr (SEP) {
-                        ru = ku * su_step;
-                        rv = kv * sv_step;
-                    } else {
-                        ru = kv * sv_step + ku * su_step;
-                    }
                 };
 
-                // tap of slot k for a record (uniform base + 32-bit lane offset)
-                auto tap = [&](const RecMeta m, const int k) {
-                    if constexpr (SEP) {
-                        const char *tu = tbase + (size_t)(m.toff & 0xffffu) * kElem;
-                        const char *tv = tbase + (size_t)(m.toff >> 16) * kElem;
-                        const uint32_t ou = lo[k] - ru, ov = lov[k] - rv;
-                        return make_float2(TapTraits<TapT>::real((const TapT *)(tu + ou), 0) *
-                                               TapTraits<TapT>::real((const TapT *)(tv + ov), 0),
-                                           0.0f);
+                // A record's tap offset, relative to a slot's term, modulo 2^32:
+                // computed by one lane per record, read back as a scalar.
+                //   LDS: bytes into the plane's table; the conjugated copy of
+                //   the bank (w < 0) is the sign of the imaginary taps, carried
+                //   by the column they multiply
+                //   global, separable: bytes of the u table, of the v table in offv
+                //   global, W-projection: bytes relative to the record's phase,
+                //   the phase (an element of the bank's table) in offv
+                auto tap_term = [&](const RecMeta m, uint32_t *offv) {
+                    const uint32_t ku = meta_ku(m), kv = meta_kv(m);
+                    if constexpr (SEP1D) {
+                        *offv = ((m.toff >> 16) - kv) * kE;
+                        return ((m.toff & 0xffffu) - ku) * kE;
                     } else {
-                        const char *tb = tbase + (size_t)m.toff * kElem;
-                        uint32_t o = lo[k] - ru;
-                        asm volatile("" : "+v"(o));   // keeps the offset 32-bit: scalar-base load
-                        return TapTraits<TapT>::cplx((const TapT *)(tb + o), 0);
+                        *offv = m.toff;
+                        uint32_t ph = 0u;
+                        if constexpr (SEP)
+                            ph = ((m.toff >> 16) * beta + (m.toff & 0xffffu)) * (uint32_t)S;
+                        else if constexpr (LDS)
+                            ph = m.toff - tap_off - (m.toff >= prm.conj_base ? prm.conj_base : 0u);
+                        return (ph - kv * (uint32_t)S - ku) * kE;
                     }
                 };
-                auto madd = [&](const int k, const float2 w, const RecVis &f) {
-                    if constexpr (SEP)
-                        fma_real(acc[k], w.x, f);
-                    else
-                        fma_complex(acc[k], w, f);
+                // taps of every slot for the record whose term is (t, tv)
+                auto issue = [&](const uint32_t t, const uint32_t tv, float2 (&w)[KD]) {
+#pragma unroll
+                    for (int k = 0; k < KD; ++k) {
+                        if constexpr (LDS) {
+                            const char *at = s_tab + (lo[k] + t);
+                            if constexpr (SEP)
+                                w[k] = make_float2(*reinterpret_cast<const float *>(at), 0.0f);
+                            else
+                                w[k] = TapTraits<TapT>::cplx(reinterpret_cast<const TapT *>(at), 0);
+                        } else if constexpr (SEP) {
+                            uint32_t ou = lo[k] + t, ov = lov[k] + tv;
+                            asm volatile("" : "+v"(ou));   // keeps the offset 32-bit: scalar-base load
+                            asm volatile("" : "+v"(ov));
+                            w[k] = make_float2(TapTraits<TapT>::real((const TapT *)(tbase + ou), 0) *
+                                                   TapTraits<TapT>::real((const TapT *)(tbase + ov), 0),
+                                               0.0f);
+                        } else {
+                            const char *tb = tbase + (size_t)tv * kE;
+                            uint32_t o = lo[k] + t;
+                            asm volatile("" : "+v"(o));
+                            w[k] = TapTraits<TapT>::cplx((const TapT *)(tb + o), 0);
+                        }
+                    }
+                };
+                // (wr + j wi)(vr + j vi) = wr (vr, vi) + wi (-vi, vr): the
+                // record's columns are blocks 2 HALF and 2 HALF + 1 of a and as
+                auto madd = [&](const float2 (&w)[KD], const float a, const float as, auto half_t) {
+                    constexpr int B0 = 2 * decltype(half_t)::value;
+                    if constexpr (!SEP) {
+#pragma unroll
+                        for (int k = 0; k < KD; ++k) {
+                            acc0[k] = mfma_col<B0>(as, w[k].y, acc0[k]);
+                            acc1[k] = mfma_col<B0 + 1>(as, w[k].y, acc1[k]);
+                        }
+                    }
+#pragma unroll
+                    for (int k = 0; k < KD; ++k) {
+                        acc0[k] = mfma_col<B0>(a, w[k].x, acc0[k]);
+                        acc1[k] = mfma_col<B0 + 1>(a, w[k].x, acc1[k]);
+                    }
                 };
 
                 const uint32_t len = ch.len;
                 const uint32_t rb = ch.start + (uint32_t)(((uint64_t)len * team) / NTEAMS);
                 const uint32_t re = ch.start + (uint32_t)(((uint64_t)len * (team + 1)) / NTEAMS);
                 if (rb < re) {
-                    // records are read in batches on the scalar unit; the next
-                    // batch's loads are issued after the current batch has been
-                    // consumed (scalar loads complete out of order: waiting for
-                    // one is waiting for all), so they overlap the current
-                    // batch's multiply-adds
-                    RecMeta nm[kBatch];
-                    float4 na4[kBatch], nb4[kBatch];
-                    // the record arrays are padded (kRecPad entries), so a batch
-                    // may run past the chunk's end (those records are not used)
-                    const RecMeta *pm = smeta + rb;
-                    const float4 *pv = svis + 2 * (size_t)rb;
-                    auto load_batch = [&]() {
-#pragma unroll
-                        for (int i = 0; i < kBatch; ++i) {
-                            nm[i] = pm[i];
-                            na4[i] = pv[2 * i];
-                            nb4[i] = pv[2 * i + 1];
-                        }
-                        pm += kBatch;
-                        pv += 2 * kBatch;
+                    // eight records at a time: lane 8 i + c of `a` holds
+                    // component c of record i; lanes past the range repeat its
+                    // end.  Records go in pairs: the pair's columns are in
+                    // lanes 0-15, and the register turns by 16 lanes after each
+                    // pair (the block of an A column is an immediate of the
+                    // instruction).
+                    uint32_t last_kuv = kNoCell;
+                    auto load_vis = [&](uint32_t r) {
+                        return svis[min((uint64_t)8 * r + lane, (uint64_t)8 * re - 1)];
                     };
-                    load_batch();
-                    wait_scalar_loads();
-                    for (uint32_t r = rb; r < re; r += kBatch) {
-                        RecMeta mm[kBatch];
-                        float4 va4[kBatch], vb4[kBatch];
-#pragma unroll
-                        for (int i = 0; i < kBatch; ++i) {
-                            mm[i] = nm[i];
-                            va4[i] = na4[i];
-                            vb4[i] = nb4[i];
+                    // n records whose meta is in lanes l0 .. l0 + n - 1 of m
+                    // (terms t, tv), moved where bit l0 + i of `moves` is set
+                    auto eight = [&](const uint32_t n, const uint32_t l0, const uint32_t kuv,
+                                     const uint32_t t, const uint32_t tv, const uint32_t moves,
+                                     float a, float as) {
+                        auto fetch = [&](uint32_t i, float2 (&w)[KD]) {
+                            issue(__builtin_amdgcn_readlane(t, i),
+                                  LDS ? 0u : __builtin_amdgcn_readlane(tv, i), w);
+                        };
+                        auto turn = [&]() {
+                            a = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute(
+                                rot16, (int)__float_as_uint(a)));
+                            if constexpr (!SEP)
+                                as = __uint_as_float((uint32_t)__builtin_amdgcn_ds_bpermute(
+                                    rot16, (int)__float_as_uint(as)));
+                        };
+                        float2 w[KD];
+                        auto step = [&](uint32_t i, auto half_t) {
+                            if ((moves >> (l0 + i)) & 1u)
+                                window_update(__builtin_amdgcn_readlane(kuv, l0 + i));
+                            fetch(l0 + i, w);
+                            madd(w, a, as, half_t);
+                        };
+                        for (uint32_t i = 0; i < n; i += 2) {
+                            step(i, std::integral_constant<int, 0>{});
+                            if (i + 1 < n) {
+                                step(i + 1, std::integral_constant<int, 1>{});
+                                turn();
+                            }
                         }
-                        __builtin_amdgcn_sched_barrier(0);
-                        load_batch();
+                    };
+                    // (-im, re) columns: neighbours swapped, the first negated
+                    auto swapped = [&](float a, uint32_t sign) {
+                        return __uint_as_float(sign ^ (uint32_t)__builtin_amdgcn_update_dpp(
+                                                          0, (int)__float_as_uint(a), 0xb1, 0xf,
+                                                          0xf, false));
+                    };
+                    // bit i: the cell of the record in lane i differs from the
+                    // previous record's
+                    auto cell_changes = [&](uint32_t kuv) {
+                        const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(
+                            (int)last_kuv, (int)kuv, 0x138, 0xf, 0xf, false);   // wave_shr:1
+                        return (uint32_t)__ballot(kuv != prev);
+                    };
+                    if constexpr (LDS) {
+                        // the next eight records are loaded while these are used
+                        // (their loads count apart from the taps' LDS reads)
+                        RecMeta mn;
+                        float an;
+                        uint32_t tn = 0;
+                        auto load = [&](uint32_t r) {
+                            mn = smeta[min(r + (uint32_t)(lane & 7), re - 1)];
+                            an = load_vis(r);
+                            if constexpr (!SEP)
+                                tn = smeta[min(r + (uint32_t)(lane >> 3), re - 1)].toff;
+                        };
+                        load(rb);
+                        for (uint32_t r = rb; r < re; r += 8) {
+                            const RecMeta mg = mn;
+                            const float a = an;
+                            float as = 0.0f;
+                            if constexpr (!SEP)
+                                as = swapped(a, swap_sign ^
+                                                    (tn >= prm.conj_base ? 0x80000000u : 0u));
+                            const uint32_t n = min(8u, re - r);
+                            uint32_t tv;
+                            const uint32_t t = tap_term(mg, &tv);
+                            const uint32_t moves = cell_changes(mg.kuv);
+                            last_kuv = __builtin_amdgcn_readlane(mg.kuv, n - 1);
+                            if (r + 8 < re) load(r + 8);
+                            eight(n, 0, mg.kuv, t, tv, moves, a, as);
+                        }
+                    } else {
+                        // loads return in order, so the taps would wait for any
+                        // records loaded ahead of them: 32 records at once
+                        for (uint32_t r = rb; r < re; r += 32) {
+                            const RecMeta mg = smeta[min(r + (uint32_t)(lane & 31), re - 1)];
+                            float av[4];
 #pragma unroll
-                        for (int i = 0; i < kBatch; ++i) {
-                            if (r + (uint32_t)i < re) {
-                                window_update(mm[i]);
-                                const RecVis f = unpack_vis(va4[i], vb4[i]);
-                                float2 w[KD];
-#pragma unroll
-                                for (int k = 0; k < KD; ++k)
-                                    w[k] = tap(mm[i], k);
-#pragma unroll
-                                for (int k = 0; k < KD; ++k)
-                                    madd(k, w[k], f);
+                            for (int g = 0; g < 4; ++g) av[g] = load_vis(r + 8 * g);
+                            uint32_t tv;
+                            const uint32_t t = tap_term(mg, &tv);
+                            const uint32_t moves = cell_changes(mg.kuv);
+                            const uint32_t n = min(32u, re - r);
+                            last_kuv = __builtin_amdgcn_readlane(mg.kuv, n - 1);
+                            for (uint32_t g = 0; g < n; g += 8) {
+                                eight(min(8u, n - g), g, mg.kuv, t, tv, moves, av[0],
+                                      SEP ? 0.0f : swapped(av[0], swap_sign));
+                                av[0] = av[1];
+                                av[1] = av[2];
+                                av[2] = av[3];
                             }
                         }
                     }
 #pragma unroll
                     for (int k = 0; k < KD; ++k)
                         if (((valid_bits >> k) & 1u) && cell[k] != kNoCell)
-                            commit(acc[k], cell[k]);
+                            commit(acc0[k], acc1[k], cell[k]);
                 }
             };
             const int kdyn = (q_ + kWave - 1) / kWave;
-            if constexpr (KMAX == 1) {
-                run(std::integral_constant<int, 1>{});
-            } else if constexpr (KMAX == 4) {
-                switch (kdyn) {
-                case 1: run(std::integral_constant<int, 1>{}); break;
-                case 2: run(std::integral_constant<int, 2>{}); break;
-                case 3: run(std::integral_constant<int, 3>{}); break;
-                default: run(std::integral_constant<int, 4>{}); break;
+            auto run_kd = [&](auto lds_t) {
+                if constexpr (KMAX == 1) {
+                    run(std::integral_constant<int, 1>{}, lds_t);
+                } else if constexpr (KMAX == 4) {
+                    switch (kdyn) {
+                    case 1: run(std::integral_constant<int, 1>{}, lds_t); break;
+                    case 2: run(std::integral_constant<int, 2>{}, lds_t); break;
+                    case 3: run(std::integral_constant<int, 3>{}, lds_t); break;
+                    default: run(std::integral_constant<int, 4>{}, lds_t); break;
+                    }
+                } else {
+                    static_assert(KMAX == 8, "slot counts 1..8");
+                    switch (kdyn) {
+                    case 1: run(std::integral_constant<int, 1>{}, lds_t); break;
+                    case 2: run(std::integral_constant<int, 2>{}, lds_t); break;
+                    case 3: run(std::integral_constant<int, 3>{}, lds_t); break;
+                    case 4: run(std::integral_constant<int, 4>{}, lds_t); break;
+                    case 5: run(std::integral_constant<int, 5>{}, lds_t); break;
+                    case 6: run(std::integral_constant<int, 6>{}, lds_t); break;
+                    case 7: run(std::integral_constant<int, 7>{}, lds_t); break;
+                    default: run(std::integral_constant<int, 8>{}, lds_t); break;
+                    }
                 }
-            } else {
-                static_assert(KMAX == 8, "slot counts 1..8");
-                switch (kdyn) {
-                case 1: run(std::integral_constant<int, 1>{}); break;
-                case 2: run(std::integral_constant<int, 2>{}); break;
-                case 3: run(std::integral_constant<int, 3>{}); break;
-                case 4: run(std::integral_constant<int, 4>{}); break;
-                case 5: run(std::integral_constant<int, 5>{}); break;
-                case 6: run(std::integral_constant<int, 6>{}); break;
-                case 7: run(std::integral_constant<int, 7>{}); break;
-                default: run(std::integral_constant<int, 8>{}); break;
-                }
-            }
+            };
+            // (the eight-slot class has no room for a table beside its region)
+            if constexpr (KMAX == 8)
+                run_kd(std::false_type{});
+            else if (in_lds)
+                run_kd(std::true_type{});
+            else
+                run_kd(std::false_type{});
         }
 
         if (use_lds) {
@@ -882,12 +1051,16 @@ struct GridPtrs {
     uint32_t *queue;             // this launch's unit counter
 };
 
+// `table`: bytes of the largest tap table of the launch's planes that fits
+// beside the region with two workgroups to a CU (0: none).
 template <int KMAX, int TEAM, bool SEP, typename TapT>
-void launch_window(const GridPtrs &a, const GridParams &prm, size_t lds, hipStream_t stream) {
+void launch_window(const GridPtrs &a, GridParams prm, size_t table, hipStream_t stream) {
     auto kern = grid_window_kernel<KMAX, TEAM, SEP, TapT>;
-    const int threads = kWave * window_waves(TEAM);
+    const int threads = kWave * kWindowWaves;
+    prm.tab_bytes = (uint32_t)table;
+    const size_t lds = window_lds(KMAX) + table;
     hipLaunchKernelGGL(kern, dim3(resident_groups((const void *)kern, threads, lds)),
-                       dim3(threads), lds, stream, a.smeta, a.svis, a.grid, (const TapT *)a.taps,
+                       dim3(threads), lds, stream, a.smeta, (const float *)a.svis, a.grid, (const TapT *)a.taps,
                        a.chunks, a.bucket_cfirst, a.units, a.group_nunits, a.planes, a.uinfo,
                        a.queue, prm);
 }
@@ -909,15 +1082,25 @@ inline int region_blocks(int T, int S) {
 
 template <bool SEP, typename TapT>
 hipError_t launch_class(int cls, const GridPtrs &a, const GridParams &prm, int smax, int tile,
-                        hipStream_t stream) {
+                        const PlaneLayout *planes, hipStream_t stream) {
+    // largest tap table, in bytes, that fits the LDS left by the region
+    auto table = [&](size_t region) {
+        size_t most = 0;
+        for (int p = prm.p_lo; p < prm.p_hi; ++p) {
+            const size_t w = (size_t)prm.beta * planes[p].S;
+            const size_t t = w * w * (SEP ? sizeof(float) : 2 * sizeof(TapT));
+            if (region + t <= kWindowLds) most = std::max(most, t);
+        }
+        return (most + 7) & ~size_t(7);
+    };
     // LDS region of the window gridders: 8 planes of the instance's fixed
     // stride (tile plus the class's largest halo)
     if (cls <= 2 && (tile != kWindowTile || smax > window_smax(cls == 0 ? 1 : cls == 1 ? 4 : 8)))
         return hipErrorInvalidValue;
     switch (cls) {
-    case 0: launch_window<1, 1, SEP, TapT>(a, prm, window_lds(1), stream); break;
-    case 1: launch_window<4, 1, SEP, TapT>(a, prm, window_lds(4), stream); break;
-    case 2: launch_window<8, 2, SEP, TapT>(a, prm, window_lds(8), stream); break;
+    case 0: launch_window<1, 1, SEP, TapT>(a, prm, table(window_lds(1)), stream); break;
+    case 1: launch_window<4, 1, SEP, TapT>(a, prm, table(window_lds(4)), stream); break;
+    case 2: launch_window<8, 2, SEP, TapT>(a, prm, 0, stream); break;
     default:
         if (region_blocks(tile, smax) > 7 * 16) return hipErrorInvalidValue;
         launch_block<7, 16, SEP, TapT>(a, prm, stream);
@@ -928,11 +1111,11 @@ hipError_t launch_class(int cls, const GridPtrs &a, const GridParams &prm, int s
 
 template <bool SEP>
 hipError_t launch_class_t(mg_dtype dt, int cls, const GridPtrs &a, const GridParams &prm,
-                          int smax, int tile, hipStream_t stream) {
+                          int smax, int tile, const PlaneLayout *planes, hipStream_t stream) {
     switch (dt) {
-    case MG_F16: return launch_class<SEP, __half>(cls, a, prm, smax, tile, stream);
-    case MG_BF16: return launch_class<SEP, __hip_bfloat16>(cls, a, prm, smax, tile, stream);
-    default: return launch_class<SEP, float>(cls, a, prm, smax, tile, stream);
+    case MG_F16: return launch_class<SEP, __half>(cls, a, prm, smax, tile, planes, stream);
+    case MG_BF16: return launch_class<SEP, __hip_bfloat16>(cls, a, prm, smax, tile, planes, stream);
+    default: return launch_class<SEP, float>(cls, a, prm, smax, tile, planes, stream);
     }
 }
 
@@ -988,7 +1171,8 @@ mg_status launch_grid(const PlanState &P, const void *vis, void *grid, void *scr
                            gs.svis, gs.uinfo);
     GridPtrs a{P.smeta,   gs.svis,        (float *)grid, P.taps,   P.chunks, P.bucket_cfirst,
                P.units,   P.group_nunits, P.d_planes,   gs.uinfo, nullptr};
-    GridParams prm{P.geom.npol, P.geom.nu, P.geom.nv, P.geom.beta, 0, 0};
+    GridParams prm{P.geom.npol, P.geom.nu, P.geom.nv, P.geom.beta, 0, 0,
+                   (uint32_t)P.geom.conj_base, 0};
     // one launch per run of consecutive planes of the same class
     int p0 = 0;
     while (p0 < np && e == hipSuccess) {
@@ -1002,8 +1186,10 @@ mg_status launch_grid(const PlanState &P, const void *vis, void *grid, void *scr
         prm.p_hi = p1;
         const int cls = P.planes[p0].cls;
         a.queue = gs.queues + p0;
-        e = sep ? launch_class_t<true>(P.tap_dtype, cls, a, prm, smax, P.planes[p0].T, stream)
-                : launch_class_t<false>(P.tap_dtype, cls, a, prm, smax, P.planes[p0].T, stream);
+        e = sep ? launch_class_t<true>(P.tap_dtype, cls, a, prm, smax, P.planes[p0].T,
+                                       P.planes.data(), stream)
+                : launch_class_t<false>(P.tap_dtype, cls, a, prm, smax, P.planes[p0].T,
+                                        P.planes.data(), stream);
         p0 = p1;
     }
     if (e == hipSuccess) e = hipGetLastError();
