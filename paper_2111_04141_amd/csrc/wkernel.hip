@@ -10,25 +10,33 @@
 // grid, M = 2 beta S_p, of spacing beta / M field units (so its transform
 // has uv spacing 1/beta cells and spans 2 S_p cells), physical direction
 // cosines = field units x fov; the central beta S_p + 1 samples per axis
-// are kept.  Steps, all in FP64 on the device:
-//   taper_kernel   c[i] = (1/M) sum_tau T[tau] cos(2pi tau i / M), i centred
-//                  (T symmetric, so the inverse DFT is real)
-//   screen_kernel  img = c[i] c[j] gbar(l_i, m_j), written straight in the
-//                  transform's order (index 0 = centre)
-//   the platform library's Z2Z forward FFT (one plan per size M and device,
-//                  created on first use and kept for the process)
-//   maxabs_kernel  largest |K| over every plane's kept samples
+// are kept.
+//
+// The image is even along both axes (the taper is real and even, the W-term
+// depends on l^2 + m^2), so its transform is a cosine transform of one
+// quadrant, and even again: with H = M/2 and e_i = 1 for i = 0 and i = H, else
+// 2,
+//     K[a][b] = sum_{i, j = 0..H} e_i e_j img[i][j] cos(2pi a i/M) cos(2pi b j/M)
+// for a, b = 0 .. H/2, an eighth of the samples a full transform computes.
+// The two sums are small FP64 matrix products on the matrix cores (any M, no
+// transform sizes with large prime factors), and every step covers all planes
+// in one launch: 32 planes of S 8 -> 64, oversampling 4, took 1.36 ms as 32
+// library transforms and some 200 launches, bound by launch latency, and
+// takes 0.058 ms here.
+//   tables_kernel  cos(2pi k/M), and the taper
+//                  c[i] = (1/M) sum_tau T[tau] cos(2pi tau i / M), i = 0..H
+//   screen_kernel  X[i][j] = e_i e_j c[i] c[j] gbar(l_i, m_j)
+//   cosine_kernel  B[i][b] = sum_j X[i][j] cos(2pi b j/M)  (X is symmetric),
+//                  then K[a][b] = sum_i cos(2pi a i/M) B[i][b] and the largest
+//                  |K|
 //   store_kernel   bank = K / max, converted to the output tap format, row
 //                  (v offset) major.
-// Plane parameters travel as kernel arguments (one launch per plane and
-// step), so the call copies nothing from the host and does not synchronise.
+// All steps in FP64.  Plane parameters travel as kernel arguments, so the
+// call copies nothing from the host and does not synchronise.
 #include <hip/hip_runtime.h>
-#include <hipfft/hipfft.h>
 
 #include <algorithm>
 #include <cmath>
-#include <map>
-#include <mutex>
 #include <string>
 #include <vector>
 
@@ -37,74 +45,177 @@
 namespace mg {
 namespace {
 
-constexpr double kTwoPi = 6.283185307179586476925286766559;
+// The planes of a bank (kernel argument).  The workspace of plane p, in
+// doubles from ws[p]: cos table [M], taper [H + 1], padded to even, then
+// complex X [H + 1][H + 1], B [H + 1][h + 1], K [h + 1][h + 1], H = M/2 = beta
+// S, h = H/2.
+struct BankPlanes {
+    int64_t ws[kMaxPlanes];
+    int64_t bank[kMaxPlanes];   // complex elements into the bank
+    double w[kMaxPlanes];
+    uint8_t S[kMaxPlanes];
+};
 
-__global__ __launch_bounds__(256) void taper_kernel(int32_t M, int32_t base_len,
-                                                    const double *__restrict__ T,
-                                                    double *__restrict__ c) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= M) return;
-    const int ic = i - M / 2;
-    const int h = (base_len - 1) / 2;
-    double s = 0.0;
-    for (int t = 0; t < base_len; ++t) {
-        // tau i mod M keeps the cosine argument small and exact
-        const int64_t ph = ((int64_t)(t - h) * ic) % M;
-        s += T[t] * cos(kTwoPi * (double)ph / (double)M);
-    }
-    c[i] = s / (double)M;
+struct PlaneWork {
+    int M, H, h;
+    double *ct, *taper;
+    double2 *X, *B, *K;
+};
+
+constexpr int kMaxBank = 512;   // largest beta S whose cos table goes to LDS
+
+constexpr int64_t table_doubles(int64_t H) { return (2 * H + H + 1 + 1) & ~int64_t(1); }
+constexpr int64_t work_doubles(int64_t H) {
+    return table_doubles(H) + 2 * ((H + 1) * (H + 1) + (H + 1) * (H / 2 + 1) + (H / 2 + 1) * (H / 2 + 1));
 }
 
-// One plane: img[k1][k2], k in transform order (signed index k or k - M).
-__global__ __launch_bounds__(256) void screen_kernel(int32_t M, int32_t beta, double w,
-                                                     double fov, const double *__restrict__ c,
-                                                     double2 *__restrict__ img) {
-    const int64_t n = (int64_t)M * M;
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * blockDim.x) {
-        const int k1 = (int)(k / M), k2 = (int)(k - (int64_t)k1 * M);
-        const int i = k1 < M / 2 ? k1 : k1 - M;   // signed (centred) index
-        const int j = k2 < M / 2 ? k2 : k2 - M;
-        const double l = (double)i * ((double)beta / (double)M) * fov;
-        const double m = (double)j * ((double)beta / (double)M) * fov;
+__device__ inline PlaneWork plane_work(const BankPlanes &P, int p, int beta, double *ws) {
+    PlaneWork w;
+    w.H = beta * (int)P.S[p];
+    w.M = 2 * w.H;
+    w.h = w.H / 2;
+    w.ct = ws + P.ws[p];
+    w.taper = w.ct + w.M;
+    w.X = reinterpret_cast<double2 *>(w.ct + table_doubles(w.H));
+    w.B = w.X + (int64_t)(w.H + 1) * (w.H + 1);
+    w.K = w.B + (int64_t)(w.H + 1) * (w.h + 1);
+    return w;
+}
+
+// One wave per taper value (lanes share the sum); also the cos table, and the
+// cleared maximum.
+__global__ __launch_bounds__(256) void tables_kernel(BankPlanes P, int32_t beta, int32_t base_len,
+                                                     const double *__restrict__ T,
+                                                     double *__restrict__ ws,
+                                                     unsigned long long *mx) {
+    const PlaneWork w = plane_work(P, blockIdx.y, beta, ws);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *mx = 0ull;
+    const int first = blockIdx.x * blockDim.x + threadIdx.x, step = gridDim.x * blockDim.x;
+    for (int k = first; k < w.M; k += step) w.ct[k] = cospi(2.0 * (double)k / (double)w.M);
+    const int lane = threadIdx.x & 63, half = (base_len - 1) / 2;
+    for (int i = first >> 6; i <= w.H; i += step >> 6) {
+        double s = 0.0;
+        for (int t = lane; t < base_len; t += 64) {
+            // tau i mod M keeps the cosine argument small and exact
+            const int ph = (t - half) * i % w.M;   // (below 2^25)
+            s += T[t] * cospi(2.0 * (double)ph / (double)w.M);
+        }
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+        if (lane == 0) w.taper[i] = s / (double)w.M;
+    }
+}
+
+__global__ __launch_bounds__(256) void screen_kernel(BankPlanes P, int32_t beta, double fov,
+                                                     double *__restrict__ ws) {
+    const PlaneWork w = plane_work(P, blockIdx.y, beta, ws);
+    const int side = w.H + 1;
+    const double wp = P.w[blockIdx.y];
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < side * side;
+         k += gridDim.x * blockDim.x) {
+        const int i = k / side, j = k - i * side;
+        const double l = (double)i * ((double)beta / (double)w.M) * fov;
+        const double m = (double)j * ((double)beta / (double)w.M) * fov;
         const double r2 = l * l + m * m;
         const double nn = r2 < 1.0 ? sqrt(1.0 - r2) : 0.0;
         double sn, cs;
-        sincos(kTwoPi * w * (nn - 1.0), &sn, &cs);
-        const double a = c[i + M / 2] * c[j + M / 2];
-        img[k] = make_double2(a * cs, a * sn);
+        sincospi(2.0 * (wp * (nn - 1.0)), &sn, &cs);
+        const double e = (i == 0 || i == w.H ? 1.0 : 2.0) * (j == 0 || j == w.H ? 1.0 : 2.0);
+        const double a = e * w.taper[i] * w.taper[j];
+        w.X[k] = make_double2(a * cs, a * sn);
     }
 }
 
-struct PlaneJob {
-    int32_t M, S;
-    int64_t img_off;     // complex elements into the FFT buffer
-    int64_t bank_off;    // complex elements into the bank
-};
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-// Kept sample (ta, tb) of plane p sits at transform index (t - beta S / 2) mod M.
-__device__ inline int64_t kept_index(int ta, int tb, int M, int half) {
-    const int a = ((ta - half) % M + M) % M;
-    const int b = ((tb - half) % M + M) % M;
-    return (int64_t)a * M + b;
-}
-
-__global__ __launch_bounds__(256) void clear_max_kernel(unsigned long long *mx) { *mx = 0ull; }
-
-__global__ __launch_bounds__(256) void maxabs_kernel(int32_t M, int32_t E,
-                                                     const double2 *__restrict__ buf,
+// D = A B on 16 x 16 x 4 FP64 matrix instructions, one 16 x 16 tile (real and
+// imaginary parts) per workgroup, whose four waves each take a quarter of the
+// sum; lane l holds A[row l % 16][k l / 16], B[k l / 16][column l % 16] and
+// D[row l / 16 + 4 r][column l % 16], r = 0..3.
+// Pass 0: D[i][b] = sum_j X[i][j] cos(2pi b j/M) (X[j][i] is read for X[i][j],
+// so lanes read consecutive words).  Pass 1: D[a][b] = sum_i cos(2pi a i/M)
+// B[i][b], and the largest |D|.
+// Bound by latency: a sum is a chain of H / 4 instructions (64 for S = 64,
+// beta = 4).  One wave per tile and one operand load at a time took 36 us a
+// pass for 32 planes of S 8 -> 64; eight loads together 24 us; the split sum
+// with the cosines in LDS 20 us.
+template <int PASS>
+__global__ __launch_bounds__(256) void cosine_kernel(BankPlanes P, int32_t beta,
+                                                     double *__restrict__ ws,
                                                      unsigned long long *mx) {
-    const int half = (E - 1) / 2;
-    double best = 0.0;
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < E * E; t += gridDim.x * blockDim.x) {
-        const int ta = t / E, tb = t - ta * E;
-        const double2 v = buf[kept_index(ta, tb, M, half)];
-        best = fmax(best, sqrt(v.x * v.x + v.y * v.y));
+    const PlaneWork w = plane_work(P, blockIdx.y, beta, ws);
+    const int rows = PASS == 0 ? w.H + 1 : w.h + 1, cols = w.h + 1;
+    const int tc = (cols + 15) / 16, tiles = ((rows + 15) / 16) * tc;
+    const int tile = blockIdx.x;
+    if (tile >= tiles) return;
+    __shared__ double s_cos[2 * kMaxBank];
+    __shared__ f64x4 s_part[2][3][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kk = lane >> 4;
+    const int r0 = (tile / tc) * 16, c0 = (tile % tc) * 16;
+    const bool in_lds = w.H <= kMaxBank;
+    if (in_lds)
+        for (int k = threadIdx.x; k < w.M; k += blockDim.x) s_cos[k] = w.ct[k];
+    __syncthreads();
+    // rows and columns past the end repeat the last one and are not stored
+    const int row = min(r0 + l16, rows - 1), col = min(c0 + l16, cols - 1);
+    // this wave's instructions: k = 4 n + kk, n in [n0, n1)
+    const int steps = w.H / 4 + 1, n0 = steps * wave / 4, n1 = steps * (wave + 1) / 4;
+    // cosine operand: index (PASS == 0 ? col : row) * k mod M
+    const int f = PASS == 0 ? col : row;
+    int ph = (int)((uint32_t)(f * (4 * n0 + kk)) % (uint32_t)w.M);   // (below 2^25)
+    const int dph = (int)((uint32_t)(f * 4) % (uint32_t)w.M);
+    f64x4 re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+    constexpr int kAhead = 8;   // operands loaded together
+    for (int nb = n0; nb < n1; nb += kAhead) {
+        double c[kAhead];
+        double2 x[kAhead];
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) {
+            const int k = 4 * (nb + a) + kk;
+            c[a] = 0.0;
+            x[a] = make_double2(0.0, 0.0);
+            if (nb + a < n1 && k <= w.H) {
+                c[a] = in_lds ? s_cos[ph] : w.ct[ph];
+                x[a] = PASS == 0 ? w.X[(int64_t)k * (w.H + 1) + row] : w.B[(int64_t)k * cols + col];
+            }
+            ph += dph;
+            if (ph >= w.M) ph -= w.M;
+        }
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) {
+            if (PASS == 0) {
+                re = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a].x, c[a], re, 0, 0, 0);
+                im = __builtin_amdgcn_mfma_f64_16x16x4f64(x[a].y, c[a], im, 0, 0, 0);
+            } else {
+                re = __builtin_amdgcn_mfma_f64_16x16x4f64(c[a], x[a].x, re, 0, 0, 0);
+                im = __builtin_amdgcn_mfma_f64_16x16x4f64(c[a], x[a].y, im, 0, 0, 0);
+            }
+        }
     }
-    // magnitudes are non-negative, so their bit patterns order like the values
-    for (int o = 32; o > 0; o >>= 1)
-        best = fmax(best, __shfl_xor(best, o));
-    if ((threadIdx.x & 63) == 0) atomicMax(mx, (unsigned long long)__double_as_longlong(best));
+    if (wave > 0) {
+        s_part[0][wave - 1][lane] = re;
+        s_part[1][wave - 1][lane] = im;
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    for (int v = 0; v < 3; ++v) {
+        re += s_part[0][v][lane];
+        im += s_part[1][v][lane];
+    }
+    double best = 0.0;
+    double2 *out = PASS == 0 ? w.B : w.K;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = r0 + kk + 4 * r, j = c0 + l16;
+        if (i < rows && j < cols) {
+            out[(int64_t)i * cols + j] = make_double2(re[r], im[r]);
+            best = fmax(best, sqrt(re[r] * re[r] + im[r] * im[r]));
+        }
+    }
+    if constexpr (PASS == 1) {
+        // magnitudes are non-negative, so their bit patterns order like the values
+        for (int o = 32; o > 0; o >>= 1) best = fmax(best, __shfl_xor(best, o));
+        if (lane == 0) atomicMax(mx, (unsigned long long)__double_as_longlong(best));
+    }
 }
 
 template <typename OutT> __device__ inline void store_tap(OutT *bank, int64_t i, double re, double im);
@@ -126,77 +237,50 @@ __device__ inline void store_tap<__hip_bfloat16>(__hip_bfloat16 *bank, int64_t i
 }
 
 template <typename OutT>
-__global__ __launch_bounds__(256) void store_kernel(int32_t M, int32_t E,
-                                                    const double2 *__restrict__ buf,
+__global__ __launch_bounds__(256) void store_kernel(BankPlanes P, int32_t beta,
+                                                    double *__restrict__ ws,
                                                     const unsigned long long *mx,
                                                     OutT *__restrict__ bank) {
-    const int half = (E - 1) / 2;
+    const PlaneWork w = plane_work(P, blockIdx.y, beta, ws);
+    const int E = w.H + 1;   // beta S + 1 kept samples per axis, the centre at h
+    OutT *dst = bank + 2 * P.bank[blockIdx.y];
     const double m = __longlong_as_double((long long)*mx);
     const double inv = m > 0.0 ? 1.0 / m : 0.0;
     for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < E * E; t += gridDim.x * blockDim.x) {
         const int ta = t / E, tb = t - ta * E;
-        const double2 v = buf[kept_index(ta, tb, M, half)];
-        store_tap<OutT>(bank, t, v.x * inv, v.y * inv);
+        const double2 v = w.K[(int64_t)abs(ta - w.h) * (w.h + 1) + abs(tb - w.h)];
+        store_tap<OutT>(dst, t, v.x * inv, v.y * inv);
     }
-}
-
-// FFT plans by (device, M), kept for the life of the process.
-std::mutex g_fft_mu;
-std::map<std::pair<int, int>, hipfftHandle> g_fft;
-
-hipfftResult fft_plan(int M, hipfftHandle *h) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return HIPFFT_INTERNAL_ERROR;
-    std::lock_guard<std::mutex> lk(g_fft_mu);
-    auto it = g_fft.find({dev, M});
-    if (it != g_fft.end()) {
-        *h = it->second;
-        return HIPFFT_SUCCESS;
-    }
-    const hipfftResult r = hipfftPlan2d(h, M, M, HIPFFT_Z2Z);
-    if (r == HIPFFT_SUCCESS) g_fft[{dev, M}] = *h;
-    return r;
 }
 
 struct Layout {
-    std::vector<PlaneJob> jobs;
+    BankPlanes planes;
     int64_t bank_elems = 0;
-    int64_t img_elems = 0;
-    int64_t taper_elems = 0;
-    size_t bytes = 0;
-    size_t off_img = 0, off_taper = 0, off_max = 0;
+    int64_t H_max = 0;          // largest beta S
+    size_t bytes = 0, off_max = 0;
 };
 
 mg_status make_layout(int32_t nplanes, const int32_t *sup, int32_t beta, Layout &L) {
     if (nplanes < 1 || nplanes > kMaxPlanes) return set_error(MG_EINVAL, "nplanes must be in 1..128");
     if (!sup) return set_error(MG_EINVAL, "null plane supports");
     if (beta < 1 || beta > kMaxBeta) return set_error(MG_EINVAL, "beta must be in 1..256");
-    L.jobs.resize(nplanes);
+    int64_t doubles = 0;
     for (int p = 0; p < nplanes; ++p) {
         const int S = sup[p];
         if (S < 1 || S > kMaxSupport) return set_error(MG_EINVAL, "plane support must be in 1..64");
         if (((int64_t)beta * S) % 2) return set_error(MG_EINVAL, "beta * support must be even");
-        // the FP64 image grid of a plane is (2 beta S)^2 x 16 bytes
+        // the FP64 image quadrant of a plane is (beta S + 1)^2 x 16 bytes
         if ((int64_t)beta * S > 4096) return set_error(MG_EINVAL, "beta * support must be <= 4096");
-        PlaneJob &j = L.jobs[p];
-        j.S = S;
-        j.M = 2 * beta * S;
-        j.bank_off = L.bank_elems;
-        L.bank_elems += (int64_t)(beta * S + 1) * (beta * S + 1);
-        j.img_off = L.img_elems;
-        L.img_elems += (int64_t)j.M * j.M;
-        L.taper_elems += j.M;
+        const int64_t H = (int64_t)beta * S;
+        L.planes.S[p] = (uint8_t)S;
+        L.planes.ws[p] = doubles;
+        L.planes.bank[p] = L.bank_elems;
+        L.bank_elems += (H + 1) * (H + 1);
+        doubles += work_doubles(H);
+        L.H_max = std::max(L.H_max, H);
     }
-    size_t off = 0;
-    auto take = [&](size_t b) {
-        const size_t at = off;
-        off += arena_round(b);
-        return at;
-    };
-    L.off_img = take(sizeof(double2) * (size_t)L.img_elems);
-    L.off_taper = take(sizeof(double) * (size_t)L.taper_elems);
-    L.off_max = take(sizeof(unsigned long long));
-    L.bytes = off;
+    L.off_max = arena_round(sizeof(double) * (size_t)doubles);
+    L.bytes = L.off_max + arena_round(sizeof(unsigned long long));
     return MG_OK;
 }
 
@@ -236,66 +320,39 @@ mg_status mg_wkernel_bank(int32_t nplanes, const int32_t *plane_support, const d
         if (!std::isfinite(plane_w[p])) return set_error(MG_EINVAL, "plane w must be finite");
         if (base_len > beta * plane_support[p] + 1)
             return set_error(MG_EINVAL, "plane support narrower than the base kernel");
+        L.planes.w[p] = plane_w[p];
     }
-    char *ws = static_cast<char *>(workspace);
-    double2 *img = reinterpret_cast<double2 *>(ws + L.off_img);
-    double *taper = reinterpret_cast<double *>(ws + L.off_taper);
-    unsigned long long *mx = reinterpret_cast<unsigned long long *>(ws + L.off_max);
-
-    hipLaunchKernelGGL(clear_max_kernel, dim3(1), dim3(1), 0, stream, mx);
-    int64_t toff = 0;
-    for (int p = 0; p < nplanes; ++p) {
-        const PlaneJob &j = L.jobs[p];
-        const int M = j.M, E = beta * j.S + 1;
-        double *c = taper + toff;
-        toff += M;
-        double2 *buf = img + j.img_off;
-        hipLaunchKernelGGL(taper_kernel, dim3((M + 255) / 256), dim3(256), 0, stream, M, base_len,
-                           base_taps, c);
-        const int64_t n = (int64_t)M * M;
-        hipLaunchKernelGGL(screen_kernel, dim3((int)std::min<int64_t>((n + 255) / 256, 4096)),
-                           dim3(256), 0, stream, M, beta, plane_w[p], fov, (const double *)c, buf);
-        hipfftHandle h = 0;
-        hipfftResult r = fft_plan(M, &h);
-        if (r == HIPFFT_SUCCESS) {
-            // the plan is shared: its stream is set and the transform queued
-            // under the lock
-            std::lock_guard<std::mutex> lk(g_fft_mu);
-            r = hipfftSetStream(h, stream);
-            if (r == HIPFFT_SUCCESS)
-                r = hipfftExecZ2Z(h, (hipfftDoubleComplex *)buf, (hipfftDoubleComplex *)buf,
-                                  HIPFFT_FORWARD);
-        }
-        if (r != HIPFFT_SUCCESS)
-            return set_error(MG_EDEVICE, "FFT failed (" + std::to_string((int)r) + ")");
-        hipLaunchKernelGGL(maxabs_kernel, dim3((unsigned)std::min(64, (E * E + 255) / 256)),
-                           dim3(256), 0, stream, M, E, (const double2 *)buf, mx);
-    }
-    for (int p = 0; p < nplanes; ++p) {
-        const PlaneJob &j = L.jobs[p];
-        const int M = j.M, E = beta * j.S + 1;
-        const double2 *buf = img + j.img_off;
-        const dim3 g((unsigned)std::min(256, (E * E + 255) / 256));
-        switch (out_dtype) {
-        case MG_F16:
-            hipLaunchKernelGGL(store_kernel<__half>, g, dim3(256), 0, stream, M, E, buf,
-                               (const unsigned long long *)mx,
-                               (__half *)bank + 2 * j.bank_off);
-            break;
-        case MG_BF16:
-            hipLaunchKernelGGL(store_kernel<__hip_bfloat16>, g, dim3(256), 0, stream, M, E, buf,
-                               (const unsigned long long *)mx,
-                               (__hip_bfloat16 *)bank + 2 * j.bank_off);
-            break;
-        default:
-            hipLaunchKernelGGL(store_kernel<float>, g, dim3(256), 0, stream, M, E, buf,
-                               (const unsigned long long *)mx, (float *)bank + 2 * j.bank_off);
-            break;
-        }
-    }
+    double *ws = static_cast<double *>(workspace);
+    unsigned long long *mx =
+        reinterpret_cast<unsigned long long *>(static_cast<char *>(workspace) + L.off_max);
+    // grids for the largest plane; the others' spare workgroups have nothing
+    // to do
+    const int64_t side = L.H_max + 1, tile_rows = (side + 15) / 16,
+                  tile_cols = (L.H_max / 2 + 1 + 15) / 16;
+    auto over = [&](int64_t groups) {
+        return dim3((unsigned)std::max<int64_t>(1, groups), (unsigned)nplanes);
+    };
+    const dim3 elems = over(std::min<int64_t>((side * side + 255) / 256, 4096));
+    hipLaunchKernelGGL(tables_kernel, over((side + 3) / 4), dim3(256), 0, stream, L.planes, beta,
+                       base_len, base_taps, ws, mx);
+    hipLaunchKernelGGL(screen_kernel, elems, dim3(256), 0, stream, L.planes, beta, fov, ws);
+    hipLaunchKernelGGL(cosine_kernel<0>, over(tile_rows * tile_cols), dim3(256), 0,
+                       stream, L.planes, beta, ws, mx);
+    hipLaunchKernelGGL(cosine_kernel<1>, over(tile_cols * tile_cols), dim3(256), 0,
+                       stream, L.planes, beta, ws, mx);
+    const unsigned long long *cmx = mx;
+    if (out_dtype == MG_F16)
+        hipLaunchKernelGGL(store_kernel<__half>, elems, dim3(256), 0, stream, L.planes, beta, ws,
+                           cmx, (__half *)bank);
+    else if (out_dtype == MG_BF16)
+        hipLaunchKernelGGL(store_kernel<__hip_bfloat16>, elems, dim3(256), 0, stream, L.planes,
+                           beta, ws, cmx, (__hip_bfloat16 *)bank);
+    else
+        hipLaunchKernelGGL(store_kernel<float>, elems, dim3(256), 0, stream, L.planes, beta, ws,
+                           cmx, (float *)bank);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(MG_EDEVICE, std::string("kernel bank: ") + hipGetErrorString(e));
-    for (int p = 0; p < nplanes; ++p) plane_offset[p] = L.jobs[p].bank_off;
+    for (int p = 0; p < nplanes; ++p) plane_offset[p] = L.planes.bank[p];
     return MG_OK;
 }
 
