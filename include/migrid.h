@@ -318,9 +318,10 @@ mg_status mg_corrector(int32_t n, int32_t beta, int32_t table_len, int32_t phase
 
 typedef struct mg_imager mg_imager;
 
-/* An imager for [npol][ny][nx] grids (nx, ny even): holds a batched C2C FFT
- * plan of the platform library (which allocates its own work area).  One
- * stream at a time per imager. */
+/* An imager for [npol][ny][nx] grids (nx, ny even).  Power-of-two sides (nx 64
+ * to 8192, ny 64 to 4096) are transformed by the library's own kernels; for
+ * others it holds a batched C2C FFT plan of the platform library (which
+ * allocates its own work area).  One stream at a time per imager. */
 mg_status mg_imager_create(mg_imager **im, int32_t npol, int32_t nx, int32_t ny);
 
 /* image = rows [y0, y0 + out_ny) of the centred inverse transform of grid
@@ -347,9 +348,8 @@ mg_status mg_imager_destroy(mg_imager *im);
  * The screen phase is reduced in FP64, its sine and cosine taken in FP32. */
 typedef struct mg_wstack_imager mg_wstack_imager;
 
-/* An imager for [npol][layers][ny][nx] layer grids (nx, ny even): holds a
- * batched C2C FFT plan of the platform library (which allocates its own
- * work area).  One stream at a time per imager. */
+/* An imager for [npol][layers][ny][nx] layer grids (nx, ny even), its
+ * transforms as mg_imager's.  One stream at a time per imager. */
 mg_status mg_wstack_imager_create(mg_wstack_imager **im, int32_t npol, int32_t layers,
                                   int32_t nx, int32_t ny);
 
