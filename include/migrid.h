@@ -177,6 +177,11 @@ mg_status mg_plan_create(mg_plan **plan, const mg_grid_desc *g, const mg_kernel_
  * the call.  Errors: MG_EINVAL (null pointer), MG_ENOMEM, MG_EDEVICE. */
 mg_status mg_plan_grid(const mg_plan *plan, const void *vis, void *grid, hipStream_t stream);
 
+/* mg_plan_grid of vis times *factor (DEVICE, FP64; each product rounded once to
+ * FP32); factor == NULL: mg_plan_grid. */
+mg_status mg_plan_grid_scaled(const mg_plan *plan, const void *vis, const double *factor,
+                              void *grid, hipStream_t stream);
+
 /* Degridding, the adjoint of the Gridding Step (the forward/backward pair of
  * the major-cycle residual, Section 1.6): vis_out = G^H grid, i.e.
  * vis_out[r][pol] = sum over the footprint of conj(weight) * grid (skipped
@@ -335,6 +340,18 @@ mg_status mg_imager_exec(mg_imager *im, const void *grid, void *work, void *imag
                          hipStream_t stream);
 
 mg_status mg_imager_destroy(mg_imager *im);
+
+/* ---- residual ----
+ *
+ * The two reductions of chi^2 around mg_plan_degrid (the residual of the major
+ * cycle, Section 1.6): model[i] = obs[i] - model[i] in FP32 for n complex64
+ * values, and *norm2 = sum |obs - model|^2 in FP64 (a fixed order of additions
+ * for a given n).  obs, model, norm2, workspace
+ * (mg_residual_workspace_size bytes, 8-byte aligned): DEVICE.
+ * Errors: MG_EINVAL (negative n, null pointers), MG_EDEVICE. */
+size_t mg_residual_workspace_size(void);
+mg_status mg_residual(int64_t n, const void *obs, void *model, double *norm2, void *workspace,
+                      hipStream_t stream);
 
 /* ---- W-stacking image ----
  *

