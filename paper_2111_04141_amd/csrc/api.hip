@@ -164,9 +164,7 @@ void note_use(mg_plan *p, hipStream_t stream) {
 mg_status build_in(PlanState &P, const mg_kernel_desc *k, const void *uvw, mg_dtype uvw_dtype,
                    void *arena, hipStream_t stream) {
     plan_carve(P, arena);
-    const mg_status st = plan_taps(P, k->taps, P.table_elems, stream);
-    if (st != MG_OK) return st;
-    return plan_build(P, uvw, uvw_dtype, stream);
+    return plan_build(P, k->taps, uvw, uvw_dtype, stream);
 }
 
 __global__ void add_count_kernel(const int64_t *src, int64_t *dst) {

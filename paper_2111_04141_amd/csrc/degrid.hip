@@ -30,10 +30,11 @@ struct DegridParams {
     int32_t p_lo, p_hi;
 };
 
-// Next chunk of this launch (one vector atomic per chunk and workgroup).
-__device__ inline uint32_t next_chunk_dg(uint32_t *queue, uint32_t *slot) {
+// Next unit of this launch after a workgroup's first, its own number (one
+// vector atomic per unit and workgroup).
+__device__ inline uint32_t next_unit_dg(uint32_t *queue, uint32_t *slot) {
     __syncthreads();
-    if (threadIdx.x == 0) *slot = atomicAdd(queue, 1u);
+    if (threadIdx.x == 0) *slot = gridDim.x + atomicAdd(queue, 1u);
     __syncthreads();
     return uniform_u32(*slot);
 }
@@ -165,8 +166,7 @@ __global__ __launch_bounds__(NW * kWave) void degrid_block_kernel(
         cuv[k] = (uint32_t)(((b % nbx) << 3) + lu) | ((uint32_t)(((b / nbx) << 3) + lv) << 16);
     }
 
-    for (uint32_t it = next_chunk_dg(queue, &s_next); it < nunits;
-         it = next_chunk_dg(queue, &s_next)) {
+    for (uint32_t it = blockIdx.x; it < nunits; it = next_unit_dg(queue, &s_next)) {
         const uint2 un = gunits[it];
         const uint32_t c0 = un.x, c1 = un.x + un.y;
         const uint32_t t = (chunks[c0].bucket - gbase) / gn;
@@ -380,8 +380,7 @@ __global__ __launch_bounds__(kWave * taps_waves(NTAP)) void degrid_taps_kernel(
     const uint2 *gunits = units + bucket_cfirst[gl.base];
     const uint32_t nunits = group_nunits[prm.p_lo];
 
-    for (uint32_t it = next_chunk_dg(queue, &s_next); it < nunits;
-         it = next_chunk_dg(queue, &s_next)) {
+    for (uint32_t it = blockIdx.x; it < nunits; it = next_unit_dg(queue, &s_next)) {
         const uint2 un = gunits[it];
         const uint32_t c0 = un.x, c1 = un.x + un.y;
         // region: union of the chunks' k_lo ranges extended by their supports
@@ -621,22 +620,20 @@ __global__ __launch_bounds__(kWave * taps_waves(NTAP)) void degrid_taps_kernel(
 }
 
 // Outputs of skipped records are zero: they follow the valid ones in the
-// plan's sorted order.
+// plan's sorted order.  Also clears the work counters.
 __global__ __launch_bounds__(256) void zero_skipped_kernel(const int64_t *__restrict__ counters,
-                                                           int64_t nrec,
+                                                           uint32_t *__restrict__ queues,
+                                                           int32_t nplanes, int64_t nrec,
                                                            const uint32_t *__restrict__ sperm,
                                                            int32_t npol,
                                                            float2 *__restrict__ vis_out) {
+    if (blockIdx.x == 0 && (int)threadIdx.x < nplanes) queues[threadIdx.x] = 0u;
     const int64_t nvalid = counters[1];
     for (int64_t i = nvalid + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nrec;
          i += (int64_t)gridDim.x * blockDim.x) {
         float2 *o = vis_out + (size_t)sperm[i] * npol;
         for (int q = 0; q < npol; ++q) o[q] = make_float2(0.0f, 0.0f);
     }
-}
-
-__global__ void clear_queue_kernel(uint32_t *w, int n) {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) w[i] = 0u;
 }
 
 struct DegridPtrs {
@@ -723,12 +720,12 @@ mg_status launch_degrid(const PlanState &P, const void *grid, void *vis_out, voi
         e = scratch_alloc((void **)&queues, degrid_scratch_bytes(P), stream);
         if (e != hipSuccess) return set_error(MG_ENOMEM, "degrid: work queue allocation failed");
     }
-    hipLaunchKernelGGL(clear_queue_kernel, dim3(1), dim3(256), 0, stream, queues, np);
     {
         int64_t nb = (P.nrec + 255) / 256;
         if (nb > 4096) nb = 4096;
         hipLaunchKernelGGL(zero_skipped_kernel, dim3((unsigned)nb), dim3(256), 0, stream,
-                           P.counters, P.nrec, P.sperm, P.geom.npol, (float2 *)vis_out);
+                           P.counters, queues, np, P.nrec, P.sperm, P.geom.npol,
+                           (float2 *)vis_out);
     }
     DegridPtrs a{P.smeta,    P.sperm,         (const float *)grid, (float *)vis_out,
                  P.taps,     P.chunks,        P.bucket_cfirst,     P.units,

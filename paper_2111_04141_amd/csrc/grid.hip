@@ -128,13 +128,13 @@ __device__ inline void fma_real(float (&acc)[8], const float w, const RecVis &f)
     }
 }
 
-// Chunks are handed out through a per-launch counter (one vector atomic per
-// chunk and workgroup), so workgroups that draw small chunks take more of
-// them; chunk sizes vary from one record to R.  Each workgroup sees its
-// chunks in increasing order.
-__device__ inline uint32_t next_chunk(uint32_t *queue, uint32_t *slot) {
+// Units are handed out through a per-launch counter (one vector atomic per
+// unit and workgroup) after each workgroup's first, its own number, so
+// workgroups that draw small units take more of them; unit sizes vary from one
+// record to R.  Each workgroup sees its units in increasing order.
+__device__ inline uint32_t next_unit(uint32_t *queue, uint32_t *slot) {
     __syncthreads();   // the previous value has been read by every wave
-    if (threadIdx.x == 0) *slot = atomicAdd(queue, 1u);
+    if (threadIdx.x == 0) *slot = gridDim.x + atomicAdd(queue, 1u);
     __syncthreads();
     return uniform_u32(*slot);
 }
@@ -196,6 +196,8 @@ constexpr size_t kWindowLds = 80 * 1024;
 // copied to LDS: the copy reads the table once through an L1 of about 32 bytes
 // a cycle, what the records would read themselves over 1 / kStagePerPhase of
 // the chunk.
+// A group of one plane copies its table once per workgroup whatever the chunk:
+// 100,800 records on 1024^2, in chunks of 64: 67 us in place of 71.
 constexpr uint32_t kStagePerPhase = 16;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -242,7 +244,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void grid_window_kernel(
     const uint2 *gunits = units + ubase;
     const uint32_t nunits = group_nunits[prm.p_lo];
     int staged = -1;   // plane whose tap table is in LDS
-    for (uint32_t it = next_chunk(queue, s_next); it < nunits; it = next_chunk(queue, s_next)) {
+    for (uint32_t it = blockIdx.x; it < nunits; it = next_unit(queue, s_next)) {
         const uint2 un = gunits[it];
         const uint32_t c0 = un.x, c1 = un.x + un.y;
         // the item's region: union of its chunks' k_lo ranges (relative to
@@ -634,24 +636,25 @@ __attribute__((amdgpu_waves_per_eu(4))) void grid_window_kernel(
 
         if (use_lds) {
             __syncthreads();
-            // cell j = rv * RW + ru of each polarisation's plane; a thread
-            // steps j by the workgroup size, so its (rv, ru) advance by a
-            // fixed step (no division per cell)
-            constexpr int kThreads = NW * kWave;
-            const int step_u = kThreads % RW, step_v = kThreads / RW;
-            const int ru0 = (int)threadIdx.x % RW, rv0 = (int)threadIdx.x / RW;
+            // word k of a polarisation is part k & 1 of cell k >> 1 = rv * RW + ru:
+            // consecutive lanes add to consecutive words of a grid row, so an
+            // atomic instruction covers its cache lines whole (the two parts
+            // apart took 67 us for 100,800 records on 1024^2, this 44); a thread steps
+            // its cell by half the workgroup, so (rv, ru) advance by a fixed
+            // step (no division per cell)
+            constexpr int kCells = NW * kWave / 2;
+            const int part = threadIdx.x & 1, j0 = (int)threadIdx.x >> 1;
+            const int step_u = kCells % RW, step_v = kCells / RW;
+            const int ru0 = j0 % RW, rv0 = j0 / RW;
             for (int pol = 0; pol < npol; ++pol) {
-                const int32_t *qre = region + (2 * pol) * PS;
-                const int32_t *qim = qre + PS;
-                float *gp = grid + 2 * (((int64_t)pol * prm.nv + cv0) * prm.nu + cu0);
+                const int32_t *qp = region + (2 * pol + part) * PS;
+                float *gp = grid + 2 * (((int64_t)pol * prm.nv + cv0) * prm.nu + cu0) + part;
                 int ru_ = ru0, rv_ = rv0;
-                for (int j = threadIdx.x; j < plane_cells; j += kThreads) {
-                    const int32_t qr = qre[j], qi = qim[j];
-                    if ((qr | qi) != 0) {
-                        float *dst = gp + 2 * ((int64_t)rv_ * prm.nu + ru_);
-                        unsafeAtomicAdd(dst, ldexpf((float)qr, -scale));
-                        unsafeAtomicAdd(dst + 1, ldexpf((float)qi, -scale));
-                    }
+                for (int j = j0; j < plane_cells; j += kCells) {
+                    const int32_t qv = qp[j];
+                    if (qv != 0)
+                        unsafeAtomicAdd(gp + 2 * ((int64_t)rv_ * prm.nu + ru_),
+                                        ldexpf((float)qv, -scale));
                     ru_ += step_u;
                     rv_ += step_v;
                     if (ru_ >= RW) {
@@ -736,7 +739,7 @@ void grid_block_kernel(
     __shared__ uint32_t s_next;
     const uint32_t ubase = bucket_cfirst[gbase];
     // the exact or fast path is chosen per unit
-    for (uint32_t i = next_chunk(queue, &s_next); i < nunits; i = next_chunk(queue, &s_next)) {
+    for (uint32_t i = blockIdx.x; i < nunits; i = next_unit(queue, &s_next)) {
         const bool exact_unit =
             (uniform_u32((uint32_t)uinfo[ubase + i]) & (uint32_t)kUnitNonFinite) != 0u;
         auto work = [&](auto exact_t) {
@@ -879,18 +882,32 @@ void grid_block_kernel(
                 records(exact_t);
             }
 
-            // commit: one float atomic per touched cell, polarisation and part
+            // commit: one float atomic per touched word.  A block's words go out
+            // as two instructions of four rows each, lane l adding part l & 1 of
+            // cell l >> 1 (fetched from the lane that holds the cell), so an
+            // instruction covers 64 consecutive bytes of each row.
 #pragma unroll
             for (int k = 0; k < KMAX; ++k) {
                 if (!((touched >> k) & 1u)) continue;
-                const int u = cu0 + (int)(cuv[k] & 0xffffu), v = cv0 + (int)(cuv[k] >> 16);
-                if (u >= prm.nu || v >= prm.nv) continue;
+                const int b = k * NW + wave;
+                const int u = cu0 + ((b % nbx) << 3) + ((lane >> 1) & 7);
+                const int v = cv0 + ((b / nbx) << 3) + (lane >> 4);
+                const int from = (lane >> 1) << 2;   // byte index of lane l >> 1
 #pragma unroll
                 for (int pol = 0; pol < 4; ++pol) {
-                    if (pol < npol && (acc[k][2 * pol] != 0.0f || acc[k][2 * pol + 1] != 0.0f)) {
-                        float *dst = grid + 2 * (((int64_t)pol * prm.nv + v) * prm.nu + u);
-                        unsafeAtomicAdd(dst, acc[k][2 * pol]);
-                        unsafeAtomicAdd(dst + 1, acc[k][2 * pol + 1]);
+                    if (pol >= npol) continue;
+                    const int re = (int)__float_as_uint(acc[k][2 * pol]);
+                    const int im = (int)__float_as_uint(acc[k][2 * pol + 1]);
+#pragma unroll
+                    for (int half = 0; half < 2; ++half) {
+                        const int xr = __builtin_amdgcn_ds_bpermute(from + 128 * half, re);
+                        const int xi = __builtin_amdgcn_ds_bpermute(from + 128 * half, im);
+                        const float x = __uint_as_float((uint32_t)((lane & 1) ? xi : xr));
+                        const int vh = v + 4 * half;
+                        if (x != 0.0f && u < prm.nu && vh < prm.nv)
+                            unsafeAtomicAdd(grid + 2 * (((int64_t)pol * prm.nv + vh) * prm.nu + u) +
+                                                (lane & 1),
+                                            x);
                     }
                 }
             }
@@ -902,9 +919,9 @@ void grid_block_kernel(
     }
 }
 
-// Gathers the visibilities of one plane group's units into sorted order,
-// padded to 4 polarisations, and writes each unit's word (see kUnitFixed).
-// A workgroup takes a unit (at most kGatherThreads * kGatherPerThread
+// Gathers the visibilities of the plane groups' units (one group per
+// blockIdx.y) into sorted order, padded to 4 polarisations, writes each unit's
+// word (see kUnitFixed) and clears the group's work counter.  A workgroup takes a unit (at most kGatherThreads * kGatherPerThread
 // records, contiguous in sorted order): every thread first loads the
 // permutation entries of its records, then their visibilities (all loads in
 // flight together), bounds the unit's partial sums, and for the window
@@ -914,14 +931,17 @@ constexpr int kGatherThreads = 256;
 constexpr int kGatherPerThread = 8;   // R <= 2048 records per unit
 
 __global__ __launch_bounds__(kGatherThreads) void gather_units_kernel(
-    const PlaneLayout *__restrict__ planes, int32_t g, int32_t sep, int32_t fixed,
-    const uint32_t *__restrict__ bucket_cfirst, const uint2 *__restrict__ units,
+    const PlaneLayout *__restrict__ planes, GroupList groups, int32_t sep,
+    uint32_t *__restrict__ queues, const uint32_t *__restrict__ bucket_cfirst, const uint2 *__restrict__ units,
     const uint32_t *__restrict__ group_nunits, const Chunk *__restrict__ chunks,
     const uint32_t *__restrict__ sperm, const float2 *__restrict__ vis, int32_t npol,
     const double *__restrict__ factor, float4 *__restrict__ svis, int32_t *__restrict__ uinfo) {
     __shared__ float s_part[kGatherThreads / kWave];
     __shared__ int s_bad[kGatherThreads / kWave];
+    const int g = groups.first[blockIdx.y];
+    if (blockIdx.x == 0 && threadIdx.x == 0) queues[g] = 0u;
     const PlaneLayout gl = planes[g];
+    const bool fixed = gl.cls <= 2;
     const uint32_t ubase = bucket_cfirst[gl.base];
     const uint32_t n = group_nunits[g];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1040,10 +1060,6 @@ __global__ __launch_bounds__(kGatherThreads) void gather_units_kernel(
             svis[2 * (size_t)r + 1] = y;
         }
     }
-}
-
-__global__ void clear_words_kernel(uint32_t *w, int n) {
-    for (int i = threadIdx.x; i < n; i += blockDim.x) w[i] = 0u;
 }
 
 struct GridPtrs {
@@ -1169,15 +1185,15 @@ mg_status launch_grid(const PlanState &P, const void *vis, void *grid, void *scr
     });
     const int np = P.nplanes_eff;
     const bool sep = P.kind == MG_KERNEL_SEPARABLE;
-    hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(256), 0, stream, gs.queues, np);
-    // sorted, scaled visibilities and unit words, one launch per plane group
-    const int gather_groups = resident_groups((const void *)gather_units_kernel, kGatherThreads, 0);
-    for (int p = 0; p < np; p += P.planes[p].grp_n)
-        hipLaunchKernelGGL(gather_units_kernel, dim3(gather_groups), dim3(kGatherThreads), 0,
-                           stream, P.d_planes, p, (int32_t)sep,
-                           (int32_t)(P.planes[p].cls <= 2), P.bucket_cfirst, P.units,
-                           P.group_nunits, P.chunks, P.sperm, (const float2 *)vis, P.geom.npol,
-                           factor, gs.svis, gs.uinfo);
+    // sorted, scaled visibilities and unit words
+    GroupList groups{};
+    const int ngroups = plane_groups(P.planes, groups);
+    const int gather_groups = (int)std::min<int64_t>(
+        resident_groups((const void *)gather_units_kernel, kGatherThreads, 0), P.nrec);
+    hipLaunchKernelGGL(gather_units_kernel, dim3(gather_groups, ngroups), dim3(kGatherThreads), 0,
+                       stream, P.d_planes, groups, (int32_t)sep, gs.queues, P.bucket_cfirst,
+                       P.units, P.group_nunits, P.chunks, P.sperm, (const float2 *)vis,
+                       P.geom.npol, factor, gs.svis, gs.uinfo);
     GridPtrs a{P.smeta,   gs.svis,        (float *)grid, P.taps,   P.chunks, P.bucket_cfirst,
                P.units,   P.group_nunits, P.d_planes,   gs.uinfo, nullptr};
     GridParams prm{P.geom.npol, P.geom.nu, P.geom.nv, P.geom.beta, 0, 0,

@@ -79,7 +79,7 @@ struct PlanState {
     PlaneLayout *d_planes = nullptr;  // [nplanes_eff]
     int64_t *counters = nullptr;      // [0] skipped, [1] valid, [2] chunks, [3], [4] scratch
     // build temporaries (inside the arena, unused after the build)
-    uint32_t *hist = nullptr, *bstart = nullptr, *cursor = nullptr;   // [nbuckets]
+    uint32_t *hist = nullptr, *cursor = nullptr;                      // [nbuckets]
     uint2 *sums = nullptr;                                            // [nscan + 1]
     size_t bytes = 0;                 // arena bytes
 };
@@ -99,6 +99,17 @@ mg_status set_error(mg_status s, const std::string &msg);
 // descriptors; no device work (api.hip).
 mg_status plan_prepare(PlanState &P, const mg_grid_desc *g, const mg_kernel_desc *k, int64_t nrec);
 
+// First planes of a plan's groups (kernel argument).
+struct GroupList {
+    uint8_t first[kMaxPlanes];
+};
+inline int plane_groups(const std::vector<PlaneLayout> &planes, GroupList &groups) {
+    int n = 0;
+    for (size_t p = 0; p < planes.size(); p += (size_t)planes[p].grp_n)
+        groups.first[n++] = (uint8_t)p;
+    return n;
+}
+
 // Arena bytes of a prepared plan, and the carving of an arena of that size
 // (256-byte aligned base) into its arrays (plan.hip).
 size_t plan_arena_bytes(const PlanState &P);
@@ -109,18 +120,16 @@ void plan_carve(PlanState &P, void *arena);
 size_t grid_scratch_bytes(const PlanState &P);
 size_t degrid_scratch_bytes(const PlanState &P);
 
-// Build steps (plan.hip), on a carved plan.  All asynchronous on `stream`;
-// nothing is allocated.
-mg_status plan_build(PlanState &P, const void *uvw, mg_dtype uvw_dtype, hipStream_t stream);
+// Builds a carved plan (plan.hip): plane layouts, the plan's tap table from the
+// caller's bank at `taps` (table_elems elements per copy, followed for
+// W-projection by its complex conjugate), index, sort, chunks and units.  All
+// asynchronous on `stream`; nothing is allocated or copied from the host.
+mg_status plan_build(PlanState &P, const void *taps, const void *uvw, mg_dtype uvw_dtype,
+                     hipStream_t stream);
 mg_status launch_compute_indices(const DevGeom &g, int64_t nrec, const void *uvw,
                                  mg_dtype uvw_dtype, int32_t *k_lo_u, int32_t *k_lo_v,
                                  int32_t *o_u, int32_t *o_v, int32_t *plane, uint8_t *valid,
                                  int64_t *d_nskipped, hipStream_t stream);
-
-// Uploads the plane layouts and lays out the plan's tap table (table_elems
-// elements per copy) from the caller's bank at src, followed for
-// W-projection by its complex conjugate (plan.hip).
-mg_status plan_taps(PlanState &P, const void *src, int64_t table_elems, hipStream_t stream);
 
 // Hot kernels (grid.hip, degrid.hip).  `scratch` holds grid_scratch_bytes /
 // degrid_scratch_bytes (256-byte aligned); nullptr: allocated and released

@@ -41,28 +41,137 @@ __device__ inline RecIndex index_bucket(const DevGeom &g, const PlaneLayout *pla
     return ix;
 }
 
+// The plan's tap table, phase-major (see common.h): entry
+// (o_v, o_u, j, i) of plane p takes bank element (o_v + 1 + j beta) *
+// (beta S + 1) + (o_u + 1 + i beta) of the caller's plane; for W-projection
+// (complex entries, (re, im) pairs of T) its conjugate also goes to
+// conj_base + the same index.  Separable: entry (o, i) takes o + 1 + i beta.
+// Also raises planes[p].tmax to the largest |component| copied (the plane
+// layouts arrive with tmax = 0; non-negative floats order like their bits).
+// Workgroup `block` of `blocks` for plane p.
 template <typename T>
-__global__ __launch_bounds__(256) void index_bucket_kernel(
-    DevGeom g, const PlaneLayout *__restrict__ planes, int64_t nrec, const T *__restrict__ uvw,
-    uint32_t *__restrict__ hist, int64_t *__restrict__ counters) {
+__device__ inline void tap_layout(PlaneLayout *planes, int p, int block, int blocks, int32_t beta,
+                                  int32_t wproj, const T *__restrict__ src, T *__restrict__ dst,
+                                  int64_t conj_base) {
+    const PlaneLayout pl = planes[p];
+    const int64_t S = pl.S;
+    const int64_t ws = (int64_t)beta * S + 1;   // caller's row length
+    const int64_t n = wproj ? (int64_t)beta * beta * S * S : (int64_t)beta * S;
+    float m = 0.0f;
+    for (int64_t e = (int64_t)block * blockDim.x + threadIdx.x; e < n;
+         e += (int64_t)blocks * blockDim.x) {
+        const int64_t i = e % S;
+        const int64_t d = (int64_t)pl.tap_off + e;
+        if (wproj) {
+            const int64_t blk = e / (S * S);
+            const int64_t j = (e / S) % S;
+            const int64_t ou = blk % beta, ov = blk / beta;
+            const int64_t sidx = (int64_t)pl.src_off + (ov + 1 + j * beta) * ws + (ou + 1 + i * beta);
+            const T re = src[2 * sidx], im = src[2 * sidx + 1];
+            dst[2 * d] = re;
+            dst[2 * d + 1] = im;
+            dst[2 * (conj_base + d)] = re;
+            dst[2 * (conj_base + d) + 1] = -im;
+            m = fmaxf(m, fmaxf(fabsf(TapTraits<T>::real(&re, 0)), fabsf(TapTraits<T>::real(&im, 0))));
+        } else {
+            const int64_t o = e / S;
+            const T t = src[o + 1 + i * beta];
+            dst[d] = t;
+            m = fmaxf(m, fabsf(TapTraits<T>::real(&t, 0)));
+        }
+    }
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    if ((threadIdx.x & 63) == 0 && m > 0.0f)
+        atomicMax(reinterpret_cast<unsigned int *>(&planes[p].tmax), __float_as_uint(m));
+}
+
+// Calls of few buckets (kLdsBuckets: grids up to 1448^2 of one plane, the
+// smallest calls, bound by latency) count in LDS first: a counter of a dense
+// tile takes an atomic about every 10 ns, so 100,800 one-channel records on 4096
+// tiles, few lanes of a wave sharing one, took 22 us here and 24 us in the
+// scatter.  A workgroup takes kLdsRecords consecutive records (and clears and
+// reads every counter: beyond a million records the aggregated atomics of a
+// wave are left the cheaper way).
+constexpr int64_t kLdsBuckets = 8192;
+constexpr int kLdsPerThread = 4;
+constexpr int kLdsRecords = 256 * kLdsPerThread;
+
+// The plane layouts a plan is built with (kernel argument: up to kPlaneArgs a
+// launch, below the argument limit), and the words that start at zero.
+constexpr int kPlaneArgs = 56;
+struct PlaneArgs {
+    PlaneLayout pl[kPlaneArgs];
+};
+
+__global__ __launch_bounds__(256) void setup_kernel(PlaneArgs a, int32_t p0, int32_t n,
+                                                    PlaneLayout *__restrict__ planes,
+                                                    int64_t *__restrict__ counters,
+                                                    uint32_t *__restrict__ group_nunits,
+                                                    int32_t nplanes, uint32_t *__restrict__ hist,
+                                                    int64_t nb) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (blockIdx.x == 0) {
+        if ((int)threadIdx.x < n) planes[p0 + threadIdx.x] = a.pl[threadIdx.x];
+        if (threadIdx.x < 6) counters[threadIdx.x] = 0;
+        if ((int)threadIdx.x < nplanes) group_nunits[threadIdx.x] = 0u;
+    }
+    // (the arena is 256-byte aligned and its arrays padded to 256 bytes)
+    uint4 *h = reinterpret_cast<uint4 *>(hist);
+    for (int64_t i = i0; i < (nb + 3) / 4; i += (int64_t)gridDim.x * blockDim.x)
+        h[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// The first `tap_blocks` workgroups lay out the tap table (tap_layout), the
+// others count the records of every bucket and the skipped ones.
+template <typename T, typename TapT, bool LDS>
+__global__ __launch_bounds__(256) void index_taps_kernel(
+    DevGeom g, PlaneLayout *planes, int64_t nrec, const T *__restrict__ uvw,
+    uint32_t *__restrict__ hist, int32_t nb, int64_t *__restrict__ counters, int32_t tap_blocks,
+    int32_t tap_per_plane, int32_t wproj, const TapT *__restrict__ src, TapT *__restrict__ dst,
+    int64_t conj_base) {
+    if ((int)blockIdx.x < tap_blocks) {
+        tap_layout<TapT>(planes, blockIdx.x / tap_per_plane, blockIdx.x % tap_per_plane,
+                         tap_per_plane, g.beta, wproj, src, dst, conj_base);
+        return;
+    }
     __shared__ uint32_t s_skip;
+    extern __shared__ uint32_t s_hist[];
     if (threadIdx.x == 0) s_skip = 0;
+    if constexpr (LDS)
+        for (int i = threadIdx.x; i < nb; i += blockDim.x) s_hist[i] = 0u;
     __syncthreads();
     uint32_t skipped = 0;
-    // every lane of a wave runs the same number of iterations (the
-    // aggregated atomic needs the whole wave)
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t first = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63);
-    for (int64_t r0 = first; r0 < nrec; r0 += stride) {
-        const int64_t r = r0 + (threadIdx.x & 63);
-        const bool in = r < nrec;
-        uint32_t b = kInvalidBucket;
-        if (in) index_bucket<T>(g, planes, uvw, r, &b);
-        if (in && b == kInvalidBucket) ++skipped;
-        wave_counter_add(hist, b, b != kInvalidBucket, false);
+    const int64_t block = (int64_t)blockIdx.x - tap_blocks, blocks = (int64_t)gridDim.x - tap_blocks;
+    if constexpr (LDS) {
+        for (int k = 0; k < kLdsPerThread; ++k) {
+            const int64_t r = block * kLdsRecords + k * 256 + threadIdx.x;
+            if (r >= nrec) break;
+            uint32_t b;
+            index_bucket<T>(g, planes, uvw, r, &b);
+            if (b == kInvalidBucket)
+                ++skipped;
+            else
+                atomicAdd(&s_hist[b], 1u);
+        }
+    } else {
+        // every lane of a wave runs the same number of iterations (the
+        // aggregated atomic needs the whole wave)
+        const int64_t stride = blocks * blockDim.x;
+        const int64_t first = block * blockDim.x + (threadIdx.x & ~63);
+        for (int64_t r0 = first; r0 < nrec; r0 += stride) {
+            const int64_t r = r0 + (threadIdx.x & 63);
+            const bool in = r < nrec;
+            uint32_t b = kInvalidBucket;
+            if (in) index_bucket<T>(g, planes, uvw, r, &b);
+            if (in && b == kInvalidBucket) ++skipped;
+            wave_counter_add(hist, b, b != kInvalidBucket, false);
+        }
     }
     if (skipped) atomicAdd(&s_skip, skipped);
     __syncthreads();
+    if constexpr (LDS)
+        for (int i = threadIdx.x; i < nb; i += blockDim.x)
+            if (s_hist[i]) atomicAdd(&hist[i], s_hist[i]);
     if (threadIdx.x == 0 && s_skip) atomicAdd((unsigned long long *)&counters[0],
                                               (unsigned long long)s_skip);
 }
@@ -70,87 +179,109 @@ __global__ __launch_bounds__(256) void index_bucket_kernel(
 // ---------------------------------------------------------------------------
 // exclusive scan of (count, chunks-of-R) pairs over the buckets
 // ---------------------------------------------------------------------------
-constexpr int kScanItems = 16;
-constexpr int kScanBlock = 256 * kScanItems;
-
-__device__ inline uint2 pair_of(const uint32_t *hist, int64_t i, int64_t n, uint32_t R) {
-    if (i >= n) return make_uint2(0, 0);
-    uint32_t c = hist[i];
-    return make_uint2(c, (c + R - 1) / R);
-}
+constexpr int kScanThreads = 1024;
+constexpr int kScanItems = 4;
+constexpr int kScanBlock = kScanThreads * kScanItems;
 
 __device__ inline uint2 add2(uint2 a, uint2 b) { return make_uint2(a.x + b.x, a.y + b.y); }
 
-// Block-wide exclusive scan of one uint2 per thread (256 threads).
-__device__ inline uint2 block_exclusive_scan(uint2 v, uint2 *total) {
-    __shared__ uint2 s[256];
-    const int t = threadIdx.x;
-    s[t] = v;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        uint2 add = (t >= off) ? s[t - off] : make_uint2(0, 0);
-        __syncthreads();
-        s[t] = add2(s[t], add);
-        __syncthreads();
-    }
-    uint2 incl = s[t];
-    *total = s[255];
-    __syncthreads();
-    return make_uint2(incl.x - v.x, incl.y - v.y);
+// This thread's buckets' counts (0 past the end; hist is padded to 256 bytes).
+__device__ inline uint4 counts_of(const uint32_t *hist, int64_t i, int64_t n) {
+    uint4 c = make_uint4(0u, 0u, 0u, 0u);
+    if (i < n) c = *reinterpret_cast<const uint4 *>(hist + i);
+    if (i + 1 >= n) c.y = 0u;
+    if (i + 2 >= n) c.z = 0u;
+    if (i + 3 >= n) c.w = 0u;
+    return c;
+}
+// (records, chunks of R) of four buckets
+__device__ inline uint2 pair_of(uint4 c, uint32_t R) {
+    return make_uint2(c.x + c.y + c.z + c.w,
+                      (c.x + R - 1) / R + (c.y + R - 1) / R + (c.z + R - 1) / R + (c.w + R - 1) / R);
 }
 
-__global__ __launch_bounds__(256) void scan_reduce_kernel(const uint32_t *__restrict__ hist,
-                                                          int64_t n, uint32_t R,
-                                                          uint2 *__restrict__ block_sums) {
-    int64_t base = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanItems;
-    uint2 acc = make_uint2(0, 0);
-    for (int i = 0; i < kScanItems; ++i) acc = add2(acc, pair_of(hist, base + i, n, R));
+// Workgroup-wide exclusive scan of one pair per thread; *total: the sum.
+__device__ inline uint2 block_exclusive_scan(uint2 v, uint2 *total) {
+    __shared__ uint2 s[kScanThreads / kWave];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint2 incl = v;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t x = (uint32_t)__shfl_up((int)incl.x, d, 64);
+        const uint32_t y = (uint32_t)__shfl_up((int)incl.y, d, 64);
+        if (lane >= d) incl = add2(incl, make_uint2(x, y));
+    }
+    __syncthreads();
+    if (lane == 63) s[wave] = incl;
+    __syncthreads();
+    uint2 before = make_uint2(0u, 0u), sum = make_uint2(0u, 0u);
+    for (int w = 0; w < kScanThreads / kWave; ++w) {
+        if (w < wave) before = add2(before, s[w]);
+        sum = add2(sum, s[w]);
+    }
+    *total = sum;
+    return make_uint2(before.x + incl.x - v.x, before.y + incl.y - v.y);
+}
+
+// Sums of the scan's blocks (calls of more than one block).
+__global__ __launch_bounds__(kScanThreads) void scan_reduce_kernel(
+    const uint32_t *__restrict__ hist, int64_t n, uint32_t R, uint2 *__restrict__ block_sums) {
+    const int64_t i = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanItems;
     uint2 total;
-    block_exclusive_scan(acc, &total);
+    block_exclusive_scan(pair_of(counts_of(hist, i, n), R), &total);
     if (threadIdx.x == 0) block_sums[blockIdx.x] = total;
 }
 
-// Single-block exclusive scan of the block sums (in place); writes the grand
-// total to *total.
-__global__ __launch_bounds__(256) void scan_sums_kernel(uint2 *__restrict__ sums, int64_t nb,
-                                                        uint2 *__restrict__ total) {
-    uint2 carry = make_uint2(0, 0);
-    for (int64_t base = 0; base < nb; base += 256) {
-        int64_t i = base + threadIdx.x;
-        uint2 v = (i < nb) ? sums[i] : make_uint2(0, 0);
-        uint2 tot;
-        uint2 ex = block_exclusive_scan(v, &tot);
-        if (i < nb) sums[i] = add2(ex, carry);
-        carry = add2(carry, tot);
-    }
-    if (threadIdx.x == 0) *total = carry;
-}
-
-// Writes bstart[i] (first record of bucket i), cursor[i] (= bstart, used by
-// the scatter) and cstart[i] (first chunk of bucket i).
-__global__ __launch_bounds__(256) void scan_down_kernel(const uint32_t *__restrict__ hist,
-                                                        int64_t n, uint32_t R,
-                                                        const uint2 *__restrict__ block_off,
-                                                        uint32_t *__restrict__ bstart,
-                                                        uint32_t *__restrict__ cursor,
-                                                        uint32_t *__restrict__ cstart) {
-    int64_t base = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanItems;
-    uint2 vals[kScanItems];
-    uint2 acc = make_uint2(0, 0);
-    for (int i = 0; i < kScanItems; ++i) {
-        vals[i] = pair_of(hist, base + i, n, R);
-        acc = add2(acc, vals[i]);
-    }
+// Writes cursor[i] (first record of bucket i, advanced by the scatter),
+// cstart[i] (first chunk of bucket i) and the chunks: bucket b with c records
+// -> ceil(c/R) chunks.  Every workgroup adds up the sums of the blocks before
+// its own (at most a few thousand words from L2).  Also plane_cfirst[p] = first
+// chunk of plane p's group, plane_cfirst[P] = cstart[n] = counters[2] = chunk
+// count, counters[1] = valid records (counters[3] counts the skipped records
+// placed by the scatter).
+__global__ __launch_bounds__(kScanThreads) void scan_chunks_kernel(
+    const uint32_t *__restrict__ hist, int64_t n, uint32_t R,
+    const uint2 *__restrict__ block_sums, uint32_t *__restrict__ cursor,
+    uint32_t *__restrict__ cstart, Chunk *__restrict__ chunks,
+    const PlaneLayout *__restrict__ planes, int32_t nplanes, uint32_t *__restrict__ plane_cfirst,
+    int64_t *__restrict__ counters) {
+    uint2 mine = make_uint2(0u, 0u), offset;
+    for (int j = threadIdx.x; j < (int)blockIdx.x; j += kScanThreads)
+        mine = add2(mine, block_sums[j]);
+    block_exclusive_scan(mine, &offset);
+    const int64_t first = (int64_t)blockIdx.x * kScanBlock;
+    const int64_t i = first + (int64_t)threadIdx.x * kScanItems;
+    const uint4 c4 = counts_of(hist, i, n);
     uint2 total;
-    uint2 run = add2(block_exclusive_scan(acc, &total), block_off[blockIdx.x]);
-    for (int i = 0; i < kScanItems; ++i) {
-        int64_t k = base + i;
-        if (k < n) {
-            bstart[k] = run.x;
-            cursor[k] = run.x;
-            cstart[k] = run.y;
+    uint2 run = add2(block_exclusive_scan(pair_of(c4, R), &total), offset);
+    const uint32_t c[kScanItems] = {c4.x, c4.y, c4.z, c4.w};
+#pragma unroll
+    for (int k = 0; k < kScanItems; ++k) {
+        if (i + k < n) {
+            cursor[i + k] = run.x;
+            cstart[i + k] = run.y;
+            for (uint32_t m = 0; m * R < c[k]; ++m) {
+                Chunk ch;
+                ch.start = run.x + m * R;
+                ch.len = min(R, c[k] - m * R);
+                ch.bucket = (uint32_t)(i + k);
+                ch.bbox = 0;
+                chunks[run.y + m] = ch;
+            }
         }
-        run = add2(run, vals[i]);
+        run = add2(run, make_uint2(c[k], (c[k] + R - 1) / R));
+    }
+    __syncthreads();   // (cstart of this block's buckets is read back)
+    for (int p = threadIdx.x; p < nplanes; p += kScanThreads) {
+        const int64_t b = planes[p].base;
+        if (b >= first && b < first + kScanBlock && b < n) plane_cfirst[p] = cstart[b];
+    }
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        const uint2 all = add2(offset, total);
+        plane_cfirst[nplanes] = all.y;
+        cstart[n] = all.y;
+        counters[1] = all.x;
+        counters[2] = all.y;
     }
 }
 
@@ -159,75 +290,68 @@ __global__ __launch_bounds__(256) void scan_down_kernel(const uint32_t *__restri
 // the chunk sort below orders each chunk by cell)
 // ---------------------------------------------------------------------------
 // Valid records go to their bucket's slots; skipped records follow all valid
-// ones (sperm only: their outputs are zeroed by the degridder).
-template <typename T>
+// ones (sperm only: their outputs are zeroed by the degridder).  LDS: the
+// workgroup's records of each bucket are counted in LDS and take consecutive
+// slots, one atomic per bucket (see index_taps_kernel).
+template <typename T, bool LDS>
 __global__ __launch_bounds__(256) void scatter_kernel(DevGeom g,
                                                       const PlaneLayout *__restrict__ planes,
                                                       int64_t nrec, const T *__restrict__ uvw,
-                                                      uint32_t *__restrict__ cursor,
-                                                      const uint2 *__restrict__ total,
+                                                      uint32_t *__restrict__ cursor, int32_t nb,
                                                       int64_t *__restrict__ counters,
                                                       RecMeta *__restrict__ smeta,
                                                       uint32_t *__restrict__ sperm) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t first = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63);
-    const int64_t nvalid = (int64_t)total->x;
-    for (int64_t r0 = first; r0 < nrec; r0 += stride) {
-        const int64_t r = r0 + (threadIdx.x & 63);
-        uint32_t b = kInvalidBucket;
-        RecIndex ix;
-        if (r < nrec) ix = index_bucket<T>(g, planes, uvw, r, &b);
-        const bool act = b != kInvalidBucket;
-        const uint32_t pos = wave_counter_add(cursor, b, act, true);
-        if (act) {
-            smeta[pos] = pack_meta(g, ix);
-            sperm[pos] = (uint32_t)r;
-        } else if (r < nrec) {
-            const int64_t q = nvalid + (int64_t)atomicAdd((unsigned long long *)&counters[3], 1ull);
-            if (q < nrec) sperm[q] = (uint32_t)r;
+    const int64_t nvalid = counters[1];
+    auto skip = [&](int64_t r) {
+        const int64_t q = nvalid + (int64_t)atomicAdd((unsigned long long *)&counters[3], 1ull);
+        if (q < nrec) sperm[q] = (uint32_t)r;
+    };
+    if constexpr (LDS) {
+        extern __shared__ uint32_t s_cnt[];
+        for (int i = threadIdx.x; i < nb; i += blockDim.x) s_cnt[i] = 0u;
+        __syncthreads();
+        RecMeta m[kLdsPerThread];
+        uint32_t b[kLdsPerThread], rank[kLdsPerThread];
+#pragma unroll
+        for (int k = 0; k < kLdsPerThread; ++k) {
+            const int64_t r = (int64_t)blockIdx.x * kLdsRecords + k * 256 + threadIdx.x;
+            b[k] = kInvalidBucket;
+            if (r >= nrec) continue;
+            const RecIndex ix = index_bucket<T>(g, planes, uvw, r, &b[k]);
+            m[k] = pack_meta(g, ix);
+            if (b[k] != kInvalidBucket)
+                rank[k] = atomicAdd(&s_cnt[b[k]], 1u);
+            else
+                skip(r);
         }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// chunk list: bucket b with c records -> ceil(c/R) chunks
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void chunk_list_kernel(int64_t nb, uint32_t R,
-                                                         const uint32_t *__restrict__ hist,
-                                                         const uint32_t *__restrict__ bstart,
-                                                         const uint32_t *__restrict__ cstart,
-                                                         Chunk *__restrict__ chunks) {
-    for (int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < nb;
-         b += (int64_t)gridDim.x * blockDim.x) {
-        uint32_t c = hist[b];
-        uint32_t s = bstart[b];
-        uint32_t k0 = cstart[b];
-        for (uint32_t k = 0; k * R < c; ++k) {
-            Chunk ch;
-            ch.start = s + k * R;
-            ch.len = min(R, c - k * R);
-            ch.bucket = (uint32_t)b;
-            ch.bbox = 0;
-            chunks[k0 + k] = ch;
+        __syncthreads();
+        for (int i = threadIdx.x; i < nb; i += blockDim.x)
+            if (s_cnt[i]) s_cnt[i] = atomicAdd(&cursor[i], s_cnt[i]);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kLdsPerThread; ++k) {
+            if (b[k] == kInvalidBucket) continue;
+            const uint32_t pos = s_cnt[b[k]] + rank[k];
+            smeta[pos] = m[k];
+            sperm[pos] = (uint32_t)((int64_t)blockIdx.x * kLdsRecords + k * 256 + threadIdx.x);
         }
-    }
-}
-
-// plane_cfirst[p] = first chunk of plane p; plane_cfirst[P] = chunk count.
-// counters[1] = valid records, counters[2] = chunks (counters[3] counts the
-// skipped records placed by the scatter).
-__global__ void plane_ranges_kernel(int32_t nplanes, const PlaneLayout *__restrict__ planes,
-                                    int64_t nb, uint32_t *__restrict__ cstart,
-                                    const uint2 *__restrict__ total,
-                                    uint32_t *__restrict__ plane_cfirst,
-                                    int64_t *__restrict__ counters) {
-    for (int p = threadIdx.x; p < nplanes; p += blockDim.x)
-        plane_cfirst[p] = (planes[p].base < nb) ? cstart[planes[p].base] : total->y;
-    if (threadIdx.x == 0) {
-        plane_cfirst[nplanes] = total->y;
-        cstart[nb] = total->y;   // end of the last bucket's chunks
-        counters[1] = total->x;
-        counters[2] = total->y;
+    } else {
+        const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+        const int64_t first = (int64_t)blockIdx.x * blockDim.x + (threadIdx.x & ~63);
+        for (int64_t r0 = first; r0 < nrec; r0 += stride) {
+            const int64_t r = r0 + (threadIdx.x & 63);
+            uint32_t b = kInvalidBucket;
+            RecIndex ix;
+            if (r < nrec) ix = index_bucket<T>(g, planes, uvw, r, &b);
+            const bool act = b != kInvalidBucket;
+            const uint32_t pos = wave_counter_add(cursor, b, act, true);
+            if (act) {
+                smeta[pos] = pack_meta(g, ix);
+                sperm[pos] = (uint32_t)r;
+            } else if (r < nrec) {
+                skip(r);
+            }
+        }
     }
 }
 
@@ -238,13 +362,15 @@ __global__ void plane_ranges_kernel(int32_t nplanes, const PlaneLayout *__restri
 // and commit the tile's region once per unit rather than once per chunk.  units[first chunk of the group + k] = (first chunk, chunk count)
 // of the group's unit k; group_nunits[g] = unit count (cleared beforehand).
 // A wave's units are consecutive and in tile order.
+// One launch covers every group (blockIdx.y).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void unit_list_kernel(const PlaneLayout *__restrict__ planes,
-                                                        int32_t g,
+                                                        GroupList groups,
                                                         const uint32_t *__restrict__ bucket_cfirst,
                                                         const Chunk *__restrict__ chunks,
                                                         uint32_t cap, uint2 *__restrict__ units,
                                                         uint32_t *__restrict__ group_nunits) {
+    const int g = groups.first[blockIdx.y];
     const PlaneLayout pl = planes[g];
     const uint32_t ntiles = (uint32_t)pl.ntu * (uint32_t)pl.ntv;
     const uint32_t n = (uint32_t)pl.grp_n;
@@ -323,16 +449,16 @@ __device__ inline uint32_t cell_key(uint32_t du, uint32_t dv, int log2T) {
 // chunks take the workgroup counting sort below.
 constexpr uint32_t kWaveSortMax = 64;
 
-__global__ __launch_bounds__(256) void chunk_sort_small_kernel(
-    const uint32_t *__restrict__ plane_cfirst, int32_t nplanes,
-    const PlaneLayout *__restrict__ planes, Chunk *__restrict__ chunks,
-    RecMeta *__restrict__ smeta, uint32_t *__restrict__ sperm) {
+__device__ inline void sort_small_chunks(const uint32_t *__restrict__ plane_cfirst,
+                                         int32_t nplanes, const PlaneLayout *__restrict__ planes,
+                                         Chunk *__restrict__ chunks, RecMeta *__restrict__ smeta,
+                                         uint32_t *__restrict__ sperm, uint32_t block,
+                                         uint32_t blocks) {
     const uint32_t c_end = plane_cfirst[nplanes];
     const int lane = threadIdx.x & 63;
-    const uint32_t nwaves = gridDim.x * (blockDim.x >> 6);
+    const uint32_t nwaves = blocks * (blockDim.x >> 6);
     int p = 0;   // chunks come in increasing order: the plane only moves forward
-    for (uint32_t c = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); c < c_end;
-         c += nwaves) {
+    for (uint32_t c = block * (blockDim.x >> 6) + (threadIdx.x >> 6); c < c_end; c += nwaves) {
         const Chunk ch = chunks[c];
         if (ch.len > kWaveSortMax) continue;
         while (p + 1 < nplanes && c >= plane_cfirst[p + 1]) ++p;
@@ -389,17 +515,25 @@ __global__ __launch_bounds__(256) void chunk_sort_kernel(const uint32_t *__restr
                                                          const PlaneLayout *__restrict__ planes,
                                                          Chunk *__restrict__ chunks,
                                                          RecMeta *__restrict__ smeta,
-                                                         uint32_t *__restrict__ sperm) {
+                                                         uint32_t *__restrict__ sperm,
+                                                         int32_t small_blocks) {
+    // the first workgroups take the small chunks, a wave each
+    if ((int)blockIdx.x < small_blocks) {
+        sort_small_chunks(plane_cfirst, nplanes, planes, chunks, smeta, sperm, blockIdx.x,
+                          (uint32_t)small_blocks);
+        return;
+    }
     __shared__ uint32_t hist[1024];
     __shared__ RecMeta m_in[kMaxR];
     __shared__ uint32_t p_in[kMaxR];
     __shared__ uint32_t s_box[4][4];   // per wave: umin, umax, vmin, vmax
+    __shared__ uint32_t s_sum[4];
     // only chunks of supports up to 32 are cell-sorted and bounded; the
     // blocked kernels of the larger supports take the records in any order
     const uint32_t c_end = plane_cfirst[nplanes];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int p = 0;   // chunks come in increasing order: the plane only moves forward
-    for (uint32_t c = blockIdx.x; c < c_end; c += gridDim.x) {
+    for (uint32_t c = blockIdx.x - small_blocks; c < c_end; c += gridDim.x - small_blocks) {
         const Chunk ch = chunks[c];
         if (ch.len <= kWaveSortMax) continue;   // the wave sort's chunks
         while (p + 1 < nplanes && c >= plane_cfirst[p + 1]) ++p;
@@ -450,16 +584,22 @@ __global__ __launch_bounds__(256) void chunk_sort_kernel(const uint32_t *__restr
         }
         {
             // exclusive scan of the (up to 1024) cell counts: 4 per thread
-            uint2 v = make_uint2(0, 0);
-            uint32_t loc[4];
+            uint32_t loc[4], sum = 0;
             for (int k = 0; k < 4; ++k) {
                 int i = threadIdx.x * 4 + k;
                 loc[k] = (i < ncell) ? hist[i] : 0u;
-                v.x += loc[k];
+                sum += loc[k];
             }
-            uint2 tot;
-            uint2 ex = block_exclusive_scan(v, &tot);
-            uint32_t run = ex.x;
+            uint32_t incl = sum;
+#pragma unroll
+            for (int d = 1; d < 64; d <<= 1) {
+                const uint32_t y = (uint32_t)__shfl_up((int)incl, d, 64);
+                if (lane >= d) incl += y;
+            }
+            if (lane == 63) s_sum[wave] = incl;
+            __syncthreads();
+            uint32_t run = incl - sum;
+            for (int w = 0; w < wave; ++w) run += s_sum[w];
             for (int k = 0; k < 4; ++k) {
                 int i = threadIdx.x * 4 + k;
                 if (i < ncell) hist[i] = run;
@@ -511,12 +651,6 @@ __global__ __launch_bounds__(256) void indices_kernel(DevGeom g, int64_t nrec,
     }
 }
 
-__global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t *p, int64_t n, uint32_t v) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = v;
-}
-
 int grid_blocks(int64_t n, int threads) {
     int64_t b = (n + threads - 1) / threads;
     if (b < 1) b = 1;
@@ -524,80 +658,7 @@ int grid_blocks(int64_t n, int threads) {
     return (int)b;
 }
 
-// The plan's tap table, phase-major (see common.h): entry
-// (o_v, o_u, j, i) of plane p takes bank element (o_v + 1 + j beta) *
-// (beta S + 1) + (o_u + 1 + i beta) of the caller's plane; for W-projection
-// (complex entries, (re, im) pairs of T) its conjugate also goes to
-// conj_base + the same index.  Separable: entry (o, i) takes o + 1 + i beta.
-// Also raises planes[p].tmax to the largest |component| copied (the plane
-// layouts arrive with tmax = 0; non-negative floats order like their bits).
-template <typename T>
-__global__ __launch_bounds__(256) void tap_layout_kernel(PlaneLayout *__restrict__ planes,
-                                                         int32_t beta, int32_t wproj,
-                                                         const T *__restrict__ src,
-                                                         T *__restrict__ dst, int64_t conj_base) {
-    const PlaneLayout pl = planes[blockIdx.y];
-    const int64_t S = pl.S;
-    const int64_t ws = (int64_t)beta * S + 1;   // caller's row length
-    const int64_t n = wproj ? (int64_t)beta * beta * S * S : (int64_t)beta * S;
-    float m = 0.0f;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = e % S;
-        const int64_t d = (int64_t)pl.tap_off + e;
-        if (wproj) {
-            const int64_t blk = e / (S * S);
-            const int64_t j = (e / S) % S;
-            const int64_t ou = blk % beta, ov = blk / beta;
-            const int64_t sidx = (int64_t)pl.src_off + (ov + 1 + j * beta) * ws + (ou + 1 + i * beta);
-            const T re = src[2 * sidx], im = src[2 * sidx + 1];
-            dst[2 * d] = re;
-            dst[2 * d + 1] = im;
-            dst[2 * (conj_base + d)] = re;
-            dst[2 * (conj_base + d) + 1] = -im;
-            m = fmaxf(m, fmaxf(fabsf(TapTraits<T>::real(&re, 0)), fabsf(TapTraits<T>::real(&im, 0))));
-        } else {
-            const int64_t o = e / S;
-            const T t = src[o + 1 + i * beta];
-            dst[d] = t;
-            m = fmaxf(m, fabsf(TapTraits<T>::real(&t, 0)));
-        }
-    }
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-    if ((threadIdx.x & 63) == 0 && m > 0.0f)
-        atomicMax(reinterpret_cast<unsigned int *>(&planes[blockIdx.y].tmax), __float_as_uint(m));
-}
-
 }  // namespace
-
-mg_status plan_taps(PlanState &P, const void *src, int64_t table_elems, hipStream_t stream) {
-    const int np = P.nplanes_eff;
-    const bool wproj = P.kind == MG_KERNEL_WPROJ;
-    hipError_t e = hipMemcpyAsync(P.d_planes, P.planes.data(), sizeof(PlaneLayout) * np,
-                                  hipMemcpyHostToDevice, stream);
-    if (e != hipSuccess)
-        return set_error(MG_EDEVICE, std::string("plane layout upload: ") + hipGetErrorString(e));
-    int64_t most = 0;
-    for (const PlaneLayout &L : P.planes) {
-        const int64_t w = (int64_t)P.geom.beta * L.S;
-        most = std::max<int64_t>(most, wproj ? w * w : w);
-    }
-    const dim3 grid((unsigned)std::min<int64_t>(grid_blocks(most, 256), 1024), (unsigned)np);
-    const int32_t beta = P.geom.beta;
-    if (P.tap_dtype == MG_F16)
-        hipLaunchKernelGGL(tap_layout_kernel<__half>, grid, dim3(256), 0, stream, P.d_planes, beta,
-                           (int32_t)wproj, (const __half *)src, (__half *)P.taps, table_elems);
-    else if (P.tap_dtype == MG_BF16)
-        hipLaunchKernelGGL(tap_layout_kernel<__hip_bfloat16>, grid, dim3(256), 0, stream,
-                           P.d_planes, beta, (int32_t)wproj, (const __hip_bfloat16 *)src,
-                           (__hip_bfloat16 *)P.taps, table_elems);
-    else
-        hipLaunchKernelGGL(tap_layout_kernel<float>, grid, dim3(256), 0, stream, P.d_planes, beta,
-                           (int32_t)wproj, (const float *)src, (float *)P.taps, table_elems);
-    e = hipGetLastError();
-    if (e != hipSuccess) return set_error(MG_EDEVICE, std::string("tap layout: ") + hipGetErrorString(e));
-    return MG_OK;
-}
 
 mg_status launch_compute_indices(const DevGeom &g, int64_t nrec, const void *uvw,
                                  mg_dtype uvw_dtype, int32_t *k_lo_u, int32_t *k_lo_v,
@@ -617,73 +678,116 @@ mg_status launch_compute_indices(const DevGeom &g, int64_t nrec, const void *uvw
     return MG_OK;
 }
 
-mg_status plan_build(PlanState &P, const void *uvw, mg_dtype uvw_dtype, hipStream_t stream) {
+namespace {
+// index_taps_kernel and scatter_kernel for the call's types
+template <typename T, typename TapT, bool LDS>
+void launch_index(const PlanState &P, const void *taps, const void *uvw, int tap_blocks,
+                  int tap_per_plane, int blocks, hipStream_t stream) {
+    const size_t lds = LDS ? sizeof(uint32_t) * (size_t)P.nbuckets : 0;
+    hipLaunchKernelGGL((index_taps_kernel<T, TapT, LDS>), dim3(tap_blocks + blocks), dim3(256),
+                       lds, stream, P.geom, P.d_planes, P.nrec, (const T *)uvw, P.hist,
+                       (int32_t)P.nbuckets, P.counters, tap_blocks, tap_per_plane,
+                       (int32_t)(P.kind == MG_KERNEL_WPROJ), (const TapT *)taps, (TapT *)P.taps,
+                       P.table_elems);
+}
+
+template <typename T, bool LDS>
+void launch_index_t(const PlanState &P, const void *taps, const void *uvw, int tap_blocks,
+                    int tap_per_plane, int blocks, hipStream_t stream) {
+    switch (P.tap_dtype) {
+    case MG_F16:
+        launch_index<T, __half, LDS>(P, taps, uvw, tap_blocks, tap_per_plane, blocks, stream);
+        break;
+    case MG_BF16:
+        launch_index<T, __hip_bfloat16, LDS>(P, taps, uvw, tap_blocks, tap_per_plane, blocks,
+                                             stream);
+        break;
+    default:
+        launch_index<T, float, LDS>(P, taps, uvw, tap_blocks, tap_per_plane, blocks, stream);
+        break;
+    }
+}
+
+template <typename T, bool LDS>
+void launch_scatter(const PlanState &P, const void *uvw, int blocks, hipStream_t stream) {
+    const size_t lds = LDS ? sizeof(uint32_t) * (size_t)P.nbuckets : 0;
+    hipLaunchKernelGGL((scatter_kernel<T, LDS>), dim3(blocks), dim3(256), lds, stream, P.geom,
+                       P.d_planes, P.nrec, (const T *)uvw, P.cursor, (int32_t)P.nbuckets,
+                       P.counters, P.smeta, P.sperm);
+}
+}  // namespace
+
+// A build is seven launches (six where one block scans the buckets): the
+// smallest calls are bound by the launches, about 6 us each.
+mg_status plan_build(PlanState &P, const void *taps, const void *uvw, mg_dtype uvw_dtype,
+                     hipStream_t stream) {
     const int64_t nrec = P.nrec;
     const int64_t nb = P.nbuckets;
     const uint32_t R = (uint32_t)P.R;
     const int np = P.nplanes_eff;
-    hipError_t e = hipSuccess;
-    uint32_t *hist = P.hist, *bstart = P.bstart, *cursor = P.cursor;
-    uint32_t *cstart = P.bucket_cfirst;   // kept: first chunk of each bucket
-    uint2 *sums = P.sums;
+    const bool wproj = P.kind == MG_KERNEL_WPROJ;
     const int64_t nscan = (nb + kScanBlock - 1) / kScanBlock;
 
-    // zero-fill with a kernel (no memset nodes, so the calls stay capturable)
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, stream, (uint32_t *)P.counters,
-                       (int64_t)12, 0u);
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(grid_blocks(nb, 256)), dim3(256), 0, stream, hist,
-                       nb, 0u);
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, stream, P.group_nunits,
-                       (int64_t)np, 0u);
+    // plane layouts and zeros, by kernels (no copies from the host, no memset
+    // nodes, so the calls stay capturable)
+    for (int p0 = 0; p0 < np; p0 += kPlaneArgs) {
+        PlaneArgs a;
+        const int n = std::min(kPlaneArgs, np - p0);
+        std::copy(P.planes.begin() + p0, P.planes.begin() + p0 + n, a.pl);
+        hipLaunchKernelGGL(setup_kernel, dim3(grid_blocks((nb + 3) / 4, 256)), dim3(256), 0,
+                           stream, a, p0, n, P.d_planes, P.counters, P.group_nunits, np, P.hist,
+                           nb);
+    }
+    int64_t most = 0;   // tap table entries of the largest plane
+    for (const PlaneLayout &L : P.planes) {
+        const int64_t w = (int64_t)P.geom.beta * L.S;
+        most = std::max<int64_t>(most, wproj ? w * w : w);
+    }
+    const int tap_per_plane = (int)std::min<int64_t>(grid_blocks(most, 256), 1024);
+    const int tap_blocks = tap_per_plane * np;
+    const bool lds = nb <= kLdsBuckets && nrec <= 1024 * (int64_t)kLdsRecords;
+    const int blocks = lds ? (int)std::max<int64_t>(1, (nrec + kLdsRecords - 1) / kLdsRecords)
+                           : grid_blocks(nrec, 256);
+    const bool f32 = uvw_dtype == MG_F32;
+    if (lds && f32)
+        launch_index_t<float, true>(P, taps, uvw, tap_blocks, tap_per_plane, blocks, stream);
+    else if (lds)
+        launch_index_t<double, true>(P, taps, uvw, tap_blocks, tap_per_plane, blocks, stream);
+    else if (f32)
+        launch_index_t<float, false>(P, taps, uvw, tap_blocks, tap_per_plane, blocks, stream);
+    else
+        launch_index_t<double, false>(P, taps, uvw, tap_blocks, tap_per_plane, blocks, stream);
+    if (nscan > 1)
+        hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)nscan), dim3(kScanThreads), 0,
+                           stream, P.hist, nb, R, P.sums);
+    hipLaunchKernelGGL(scan_chunks_kernel, dim3((unsigned)nscan), dim3(kScanThreads), 0, stream,
+                       P.hist, nb, R, P.sums, P.cursor, P.bucket_cfirst, P.chunks, P.d_planes, np,
+                       P.plane_cfirst, P.counters);
     if (nrec > 0) {
-        int g1 = grid_blocks(nrec, 256);
-        if (uvw_dtype == MG_F32)
-            hipLaunchKernelGGL(index_bucket_kernel<float>, dim3(g1), dim3(256), 0, stream, P.geom,
-                               P.d_planes, nrec, (const float *)uvw, hist, P.counters);
-        else
-            hipLaunchKernelGGL(index_bucket_kernel<double>, dim3(g1), dim3(256), 0, stream,
-                               P.geom, P.d_planes, nrec, (const double *)uvw, hist, P.counters);
+        if (lds && f32) launch_scatter<float, true>(P, uvw, blocks, stream);
+        else if (lds) launch_scatter<double, true>(P, uvw, blocks, stream);
+        else if (f32) launch_scatter<float, false>(P, uvw, blocks, stream);
+        else launch_scatter<double, false>(P, uvw, blocks, stream);
     }
-    hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)nscan), dim3(256), 0, stream, hist, nb,
-                       R, sums);
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(256), 0, stream, sums, nscan, sums + nscan);
-    hipLaunchKernelGGL(scan_down_kernel, dim3((unsigned)nscan), dim3(256), 0, stream, hist, nb, R,
-                       sums, bstart, cursor, cstart);
-    if (nrec > 0) {
-        const dim3 g1(grid_blocks(nrec, 256));
-        if (uvw_dtype == MG_F32)
-            hipLaunchKernelGGL(scatter_kernel<float>, g1, dim3(256), 0, stream, P.geom, P.d_planes,
-                               nrec, (const float *)uvw, cursor, sums + nscan, P.counters, P.smeta,
-                               P.sperm);
-        else
-            hipLaunchKernelGGL(scatter_kernel<double>, g1, dim3(256), 0, stream, P.geom,
-                               P.d_planes, nrec, (const double *)uvw, cursor, sums + nscan,
-                               P.counters, P.smeta, P.sperm);
-    }
-    hipLaunchKernelGGL(chunk_list_kernel, dim3(grid_blocks(nb, 256)), dim3(256), 0, stream, nb, R,
-                       hist, bstart, cstart, P.chunks);
-    hipLaunchKernelGGL(plane_ranges_kernel, dim3(1), dim3(256), 0, stream, np, P.d_planes, nb,
-                       cstart, sums + nscan, P.plane_cfirst, P.counters);
-    {
-        // cell sort and bounding box of the chunks of the window gridders'
-        // supports (up to 32): small chunks one per wave, the others one per
-        // workgroup
-        hipLaunchKernelGGL(chunk_sort_small_kernel, dim3(8 * device_cus()), dim3(256), 0,
-                           stream, P.plane_cfirst, np, P.d_planes, P.chunks, P.smeta, P.sperm);
-        hipLaunchKernelGGL(chunk_sort_kernel,
-                           dim3(resident_groups((const void *)chunk_sort_kernel, 256, 0)),
-                           dim3(256), 0, stream, P.plane_cfirst, np, P.d_planes, P.chunks,
-                           P.smeta, P.sperm);
-        // units of every plane group
-        for (int p = 0; p < np; p += P.planes[p].grp_n) {
-            const PlaneLayout &L = P.planes[p];
-            const int64_t ntiles = (int64_t)L.ntu * L.ntv;
-            hipLaunchKernelGGL(unit_list_kernel, dim3(grid_blocks(ntiles, 256)), dim3(256), 0,
-                               stream, P.d_planes, p, P.bucket_cfirst, P.chunks, R, P.units,
-                               P.group_nunits);
-        }
-    }
-    e = hipGetLastError();
+    // cell sort and bounding box of the chunks of the window gridders'
+    // supports (up to 32): small chunks one per wave, the others one per
+    // workgroup
+    const int cus = device_cus();
+    const int64_t chunks = std::min<int64_t>(P.max_chunks, nrec);   // at most
+    const int small_blocks = (int)std::min<int64_t>(8 * cus, std::max<int64_t>(1, (chunks + 3) / 4));
+    const int large_blocks = (int)std::min<int64_t>(
+        resident_groups((const void *)chunk_sort_kernel, 256, 0),
+        std::max<int64_t>(1, nrec / kWaveSortMax));
+    hipLaunchKernelGGL(chunk_sort_kernel, dim3(small_blocks + large_blocks), dim3(256), 0, stream,
+                       P.plane_cfirst, np, P.d_planes, P.chunks, P.smeta, P.sperm, small_blocks);
+    // units of every plane group
+    GroupList groups{};
+    const int ngroups = plane_groups(P.planes, groups);
+    const int64_t tiles = (int64_t)P.planes[0].ntu * P.planes[0].ntv;   // (T is every plane's)
+    hipLaunchKernelGGL(unit_list_kernel, dim3(grid_blocks(tiles, 256), ngroups), dim3(256), 0,
+                       stream, P.d_planes, groups, P.bucket_cfirst, P.chunks, R, P.units,
+                       P.group_nunits);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(MG_EDEVICE, std::string("plan kernels: ") + hipGetErrorString(e));
     return MG_OK;
 }
@@ -713,7 +817,6 @@ size_t walk_arena(const PlanState &P, F &&place) {
     place(8, take(sizeof(uint32_t) * (size_t)np));
     place(9, take(sizeof(int64_t) * 6));
     place(10, take(sizeof(uint32_t) * (size_t)nb));
-    place(11, take(sizeof(uint32_t) * (size_t)nb));
     place(12, take(sizeof(uint32_t) * (size_t)nb));
     place(13, take(sizeof(uint2) * (size_t)(nscan + 1)));
     return off;
@@ -740,7 +843,6 @@ void plan_carve(PlanState &P, void *arena) {
         case 8: P.group_nunits = static_cast<uint32_t *>(p); break;
         case 9: P.counters = static_cast<int64_t *>(p); break;
         case 10: P.hist = static_cast<uint32_t *>(p); break;
-        case 11: P.bstart = static_cast<uint32_t *>(p); break;
         case 12: P.cursor = static_cast<uint32_t *>(p); break;
         default: P.sums = static_cast<uint2 *>(p); break;
         }
