@@ -12,8 +12,8 @@
 // per lane into the record's partial sums.  Partial sums of B records are
 // then reduced across the wave's lanes (a butterfly that halves the values
 // each lane holds at every step) and across the waves through LDS, and one
-// thread per (record, component) writes the result.  Supports up to 32 take
-// degrid_taps_kernel (below).
+// thread per (record, component) writes the result.  Supports 17 to 32 take
+// degrid_taps_kernel, up to 16 degrid_cells_kernel (below).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -28,6 +28,8 @@ namespace {
 struct DegridParams {
     int32_t npol, nu, nv, beta;
     int32_t p_lo, p_hi;
+    uint32_t conj_base;   // element offset of the conjugated copy of the bank
+    uint32_t tab_bytes;   // cells kernel: LDS for a plane's tap table
 };
 
 // Next unit of this launch after a workgroup's first, its own number (one
@@ -334,7 +336,406 @@ __global__ __launch_bounds__(NW * kWave) void degrid_block_kernel(
     }
 }
 
-// Supports up to 32: the lanes of a wave take the taps of one record (tap
+// Supports up to 16 (degrid_cells_kernel): a workgroup takes a unit (chunks of
+// one tile over the planes of the group) and stages the unit's grid region once
+// in LDS, 32 bytes a cell, [row][PITCH] cells of four float2 holding components
+// (c, c + 4), c = 2 polarisation + part.
+//
+// Records come sorted by cell, so several share a footprint.  Where the plane's
+// tap table is in LDS too, up to four records of one cell are taken together on
+// the matrix cores: v_mfma_f32_4x4x1_16b multiplies four components of 16 cells
+// (one cell per block, lane l holding component l % 4 of cell l / 4) by a tap of
+// each of the four records (lane l: record l % 4), so a cell is read from LDS
+// once for four records instead of once each; lane l ends with the components
+// of record l % 4 over every 16th cell, and a reduction over 16 lanes finishes
+// four records at once.  The real and imaginary taps sum apart (P = sum wr G,
+// Q = sum wi G), and conj(w) G is put together at the end, with the sign of Q
+// where the taps are the conjugated copy's.
+// A record on its own costs about what it does in the lane-per-tap path (below)
+// and four cost as much as one.  The lane-per-tap path reads 32 bytes of LDS a
+// tap, 18 cycles for 64 taps shared by four SIMDs against 54 cycles of
+// multiply-adds, and reduces every pair of records across the wave; it is kept
+// for chunks too short to pay for the table, and tables that do not fit.
+// Against the lane-per-tap path for all: W-projection benchmark workload (133.7M
+// records, 8192^2) S <= 8 3.87 -> 2.88 ms, S <= 16 9.88 -> 8.06 ms (runs of 8 and
+// 5 records a cell); separable 7 x 7, 10.08M records, 2048^2: 0.944 -> 0.522 ms.
+// Sixteen waves to a workgroup: 9.3 ms for S <= 16.
+//
+// Lane-per-tap path: the lanes of a wave take the taps of one record (tap
+// q = t * 64 + lane, q < S^2), so no lane sits outside a footprint; groups of B
+// records are reduced across the wave's lanes.
+constexpr int kCellWaves = 8;
+constexpr int cells_smax(int ntap) { return ntap == 1 ? 8 : 16; }
+constexpr int kCellTile = 16;
+constexpr int cells_pitch(int ntap) { return kCellTile + cells_smax(ntap) - 1; }
+// LDS of the region (bytes), before the tap table
+constexpr size_t cells_region(int ntap) {
+    return sizeof(float4) * 2 * (size_t)cells_pitch(ntap) * cells_pitch(ntap);
+}
+// LDS a workgroup's region and table may take so that two share a CU's 160 KB
+constexpr size_t kCellLds = 80 * 1024 - 256;
+// Records per oversampling phase a chunk needs for its plane's table to be
+// copied to LDS (as the window gridders': the copy reads the table once).
+constexpr uint32_t kCellStagePerPhase = 16;
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+template <int NTAP, int B, bool SEP, typename TapT>
+__global__ __launch_bounds__(kWave * kCellWaves)
+__attribute__((amdgpu_waves_per_eu(4))) void degrid_cells_kernel(
+    const RecMeta *__restrict__ smeta, const uint32_t *__restrict__ sperm,
+    const float *__restrict__ grid, float *__restrict__ vis_out, const TapT *__restrict__ taps,
+    const Chunk *__restrict__ chunks, const uint32_t *__restrict__ bucket_cfirst,
+    const uint2 *__restrict__ units, const uint32_t *__restrict__ group_nunits,
+    const PlaneLayout *__restrict__ planes, uint32_t *__restrict__ queue, DegridParams prm) {
+    constexpr int NV = B * 8;
+    constexpr int kThreads = kWave * kCellWaves;
+    constexpr int PITCH = cells_pitch(NTAP);
+    constexpr uint32_t kElem = SEP ? sizeof(TapT) : 2 * sizeof(TapT);
+    constexpr uint32_t kElemLds = SEP ? sizeof(float) : kElem;
+    constexpr int kSteps = NTAP * 4;   // 16 cells each
+    extern __shared__ float4 cells[];  // [PITCH][PITCH][2], then the tap table
+    char *const s_reg = reinterpret_cast<char *>(cells);
+    char *const s_tab = s_reg + cells_region(NTAP);
+    __shared__ uint32_t s_next;
+    const int wave = (int)uniform_u32(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    const int npol = prm.npol;
+    const uint32_t beta = (uint32_t)prm.beta;
+    const char *tbase = reinterpret_cast<const char *>(taps);
+    const PlaneLayout gl = planes[prm.p_lo];
+    const uint2 *gunits = units + bucket_cfirst[gl.base];
+    const uint32_t nunits = group_nunits[prm.p_lo];
+    int staged = -1;   // plane whose tap table is in LDS
+
+    for (uint32_t it = blockIdx.x; it < nunits; it = next_unit_dg(queue, &s_next)) {
+        const uint2 un = gunits[it];
+        const uint32_t c0 = un.x, c1 = un.x + un.y;
+        // region: union of the chunks' k_lo ranges extended by their supports
+        uint32_t umin = 0xffu, vmin = 0xffu, uend = 0u, vend = 0u;
+        for (uint32_t c = c0; c < c1; ++c) {
+            const Chunk ch = chunks[c];
+            int pc;
+            uint32_t tile_;
+            bucket_plane_tile(gl, ch.bucket, &pc, &tile_);
+            const uint32_t Sc = (uint32_t)planes[pc].S;
+            umin = min(umin, ch.bbox & 0xffu);
+            vmin = min(vmin, (ch.bbox >> 16) & 0xffu);
+            uend = max(uend, ((ch.bbox >> 8) & 0xffu) + Sc);
+            vend = max(vend, (ch.bbox >> 24) + Sc);
+        }
+        uint32_t tile;
+        {
+            int pc;
+            bucket_plane_tile(gl, chunks[c0].bucket, &pc, &tile);
+        }
+        const int cu0 = (int)(((tile % (uint32_t)gl.ntu) << gl.log2T) + umin);
+        const int cv0 = (int)(((tile / (uint32_t)gl.ntu) << gl.log2T) + vmin);
+        const int RW = (int)(uend - umin);
+        const int RH = (int)(vend - vmin);
+
+        // stage the region (cells outside it are never read); cell
+        // j = rv * RW + ru, a thread stepping j by the workgroup size and
+        // (rv, ru) by a fixed step (no division per cell)
+        {
+            const int ncells = RH * RW;
+            const int step_u = kThreads % RW, step_v = kThreads / RW;
+            int ru = (int)threadIdx.x % RW, rv = (int)threadIdx.x / RW;
+            const float2 *gp = reinterpret_cast<const float2 *>(grid) + (int64_t)cv0 * prm.nu + cu0;
+            const int64_t plane = (int64_t)prm.nv * prm.nu;
+            for (int j = threadIdx.x; j < ncells; j += kThreads) {
+                float2 x[4];
+#pragma unroll
+                for (int pol = 0; pol < 4; ++pol)
+                    x[pol] = pol < npol ? gp[pol * plane + (int64_t)rv * prm.nu + ru]
+                                        : make_float2(0.0f, 0.0f);
+                float4 *dst = cells + 2 * (rv * PITCH + ru);
+                dst[0] = make_float4(x[0].x, x[2].x, x[0].y, x[2].y);
+                dst[1] = make_float4(x[1].x, x[3].x, x[1].y, x[3].y);
+                ru += step_u;
+                rv += step_v;
+                if (ru >= RW) {
+                    ru -= RW;
+                    ++rv;
+                }
+            }
+        }
+        __syncthreads();
+
+        uint32_t turn = 0;   // the wave whose turn it is, over the unit's groups
+        for (uint32_t c = c0; c < c1; ++c) {
+            const Chunk ch = chunks[c];
+            int pc;
+            uint32_t tile_;
+            bucket_plane_tile(gl, ch.bucket, &pc, &tile_);
+            const int S = planes[pc].S;
+            const uint32_t tap_off = planes[pc].tap_off;
+            const uint32_t ntap = beta * beta * (uint32_t)(S * S);   // phase-major S x S blocks
+            bool in_lds = staged == pc;
+            if (!in_lds && (gl.grp_n == 1 || ch.len >= kCellStagePerPhase * beta * beta) &&
+                ntap * kElemLds <= prm.tab_bytes) {
+                __syncthreads();   // the previous table's readers are done
+                if constexpr (SEP) {
+                    float *t = reinterpret_cast<float *>(s_tab);
+                    for (uint32_t e = threadIdx.x; e < ntap; e += kThreads) {
+                        const uint32_t blk = e / (uint32_t)(S * S), r = e - blk * (uint32_t)(S * S);
+                        const uint32_t j = r / (uint32_t)S, i = r - j * (uint32_t)S;
+                        const uint32_t ov = blk / beta, ou = blk - ov * beta;
+                        t[e] = TapTraits<TapT>::real(taps, ou * (uint32_t)S + i) *
+                               TapTraits<TapT>::real(taps, ov * (uint32_t)S + j);
+                    }
+                } else {
+                    const uint32_t *src =
+                        reinterpret_cast<const uint32_t *>(tbase + (size_t)tap_off * kElem);
+                    uint32_t *t = reinterpret_cast<uint32_t *>(s_tab);
+                    for (uint32_t e = threadIdx.x; e < ntap * (kElem / 4); e += kThreads)
+                        t[e] = src[e];
+                }
+                __syncthreads();
+                staged = pc;
+                in_lds = true;
+            }
+
+            // up to four records of one cell at a time
+            auto by_cell = [&]() {
+                const int blk = lane >> 2, col = lane & 3;
+                const int nsteps = (S * S + 15) >> 4;
+                // this lane's cell of each step, as a byte offset from the
+                // footprint's first cell (component pair `col`); cells past the
+                // footprint read its first cell and count as zero
+                uint32_t goff[kSteps];
+#pragma unroll
+                for (int t = 0; t < kSteps; ++t) {
+                    const int q = t * 16 + blk;
+                    const int qq = q < S * S ? q : 0;
+                    const int j = qq / S;
+                    goff[t] = (uint32_t)((j * PITCH + (qq - j * S)) * 32 + col * 8);
+                }
+                const bool rest = (S * S) % 16 != 0;
+                const bool last_on = (nsteps - 1) * 16 + blk < S * S;
+                const int idx = reduce_index<8>(lane);
+                const uint32_t rb = ch.start + (uint32_t)(((uint64_t)ch.len * wave) / kCellWaves);
+                const uint32_t re = ch.start + (uint32_t)(((uint64_t)ch.len * (wave + 1)) / kCellWaves);
+                for (uint32_t r0 = rb; r0 < re; r0 += 64) {
+                    // 64 records, one per lane: LDS offsets of the footprint and
+                    // of the taps (bit 0: conjugated copy), destination
+                    const uint32_t n = min(64u, re - r0);
+                    const uint32_t r = r0 + min((uint32_t)lane, n - 1);
+                    const RecMeta m = smeta[r];
+                    const uint32_t perm = sperm[r];
+                    uint32_t ph;
+                    bool conj = false;
+                    if constexpr (SEP) {
+                        ph = ((m.toff >> 16) * beta + (m.toff & 0xffffu)) * (uint32_t)S;
+                    } else {
+                        conj = m.toff >= prm.conj_base;
+                        ph = m.toff - tap_off - (conj ? prm.conj_base : 0u);
+                    }
+                    const uint32_t tt = ph * kElemLds | (conj ? 1u : 0u);
+                    const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(
+                        -1, (int)m.kuv, 0x138, 0xf, 0xf, false);   // wave_shr:1
+                    const uint64_t starts = __ballot(m.kuv != prev || lane == 0);
+                    for (uint32_t pos = 0; pos < n;) {
+                        const uint64_t later = starts & (~0ull << pos << 1);
+                        const uint32_t end = later ? min((uint32_t)__builtin_ctzll(later), n) : n;
+                        const uint32_t g = min(4u, end - pos);
+                        const uint32_t kuv = __builtin_amdgcn_readlane(m.kuv, pos);
+                        const uint32_t cell0 = (((kuv >> 16) - (uint32_t)cv0) * PITCH +
+                                                ((kuv & 0xffffu) - (uint32_t)cu0)) * 32u;
+                        // this lane's record (the last one where there are fewer)
+                        const int from = (int)((pos + min((uint32_t)col, g - 1)) << 2);
+                        const uint32_t tj = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)tt);
+                        const uint32_t dst = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)perm);
+                        const char *tp = s_tab + (tj & ~1u) + blk * kElemLds;
+                        f32x4 p0 = {0, 0, 0, 0}, p1 = p0, q0 = p0, q1 = p0;
+                        // (compared step by step: the masks of all steps, kept
+                        // for the loop, would spill)
+                        int ns = nsteps, nrest = rest ? nsteps - 1 : -1;
+                        asm volatile("" : "+s"(ns), "+s"(nrest));
+#pragma unroll
+                        for (int t0 = 0; t0 < kSteps; t0 += 4) {
+                            if (t0 >= ns) break;
+                            float2 w[4], x[4];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                const int t = t0 + u;
+                                if (t >= ns) continue;
+                                const char *at = tp + t * 16 * (int)kElemLds;
+                                if constexpr (SEP)
+                                    w[u] = make_float2(*reinterpret_cast<const float *>(at), 0.0f);
+                                else
+                                    w[u] = TapTraits<TapT>::cplx(reinterpret_cast<const TapT *>(at), 0);
+                                x[u] = *reinterpret_cast<const float2 *>(s_reg + (goff[t] + cell0));
+                            }
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                const int t = t0 + u;
+                                if (t >= ns) continue;
+                                if (t == nrest && !last_on)
+                                    w[u] = x[u] = make_float2(0.0f, 0.0f);
+                                p0 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[u].x, w[u].x, p0, 0, 0, 0);
+                                p1 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[u].y, w[u].x, p1, 0, 0, 0);
+                                if constexpr (!SEP) {
+                                    q0 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[u].x, w[u].y, q0, 0, 0, 0);
+                                    q1 = __builtin_amdgcn_mfma_f32_4x4x1f32(x[u].y, w[u].y, q1, 0, 0, 0);
+                                }
+                            }
+                        }
+                        // conj(w) G = (wr gr + wi gi) + j (wr gi - wi gr)
+                        float v[8];
+                        const float sg = (tj & 1u) ? -1.0f : 1.0f;
+#pragma unroll
+                        for (int k = 0; k < 4; k += 2) {
+                            v[k] = SEP ? p0[k] : fmaf(sg, q0[k + 1], p0[k]);
+                            v[k + 1] = SEP ? p0[k + 1] : fmaf(-sg, q0[k], p0[k + 1]);
+                            v[k + 4] = SEP ? p1[k] : fmaf(sg, q1[k + 1], p1[k]);
+                            v[k + 5] = SEP ? p1[k + 1] : fmaf(-sg, q1[k], p1[k + 1]);
+                        }
+                        // over the lanes of the record (bits 2 to 5)
+                        reduce_step<8, 0, 4>(v, lane);
+                        v[0] += __shfl_xor(v[0], 4);
+                        if ((lane & 4) == 0 && (uint32_t)col < g && (idx >> 1) < npol)
+                            vis_out[((size_t)dst * npol + (idx >> 1)) * 2 + (idx & 1)] = v[0];
+                        pos += g;
+                    }
+                }
+            };
+
+            // one record's taps across the wave, NT per lane
+            auto by_tap = [&](auto nt_t) {
+                constexpr int NT = decltype(nt_t)::value;
+                const int my_idx = reduce_index<NV>(lane);
+                const bool writer = reduce_writer<NV>(lane);
+                // this lane's taps q = t * 64 + lane: LDS offset and table byte
+                // offset relative to the footprint's first cell and first tap.
+                // Taps t < NT - 1 lie in every footprint; where S^2 is not a
+                // multiple of 64, lanes past S^2 in the last tap read the first
+                // tap and first cell (in bounds) and their products are zeroed.
+                const bool last_full = (S * S) % 64 == 0;
+                const bool last_on = ((NT - 1) * 64 + lane) < S * S;
+                int lg[NT];
+                uint32_t lt[NT], ltv[NT];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    const int qq = (t * 64 + lane < S * S) ? t * 64 + lane : 0;
+                    const int j = qq / S, i = qq - j * S;
+                    lg[t] = 2 * (j * PITCH + i);
+                    if constexpr (SEP) {
+                        lt[t] = (uint32_t)i * kElem;
+                        ltv[t] = (uint32_t)j * kElem;
+                    } else {
+                        lt[t] = (uint32_t)(j * S + i) * kElem;
+                        ltv[t] = 0u;
+                    }
+                }
+                // groups of B records, taken by the waves in turn (continuing
+                // from the unit's previous chunk); a short last group repeats
+                // the chunk's last record (its sums are not written)
+                const uint32_t rend = ch.start + ch.len;
+                const uint32_t ngroups = (ch.len + B - 1) / B;
+                const uint32_t gfirst = ((uint32_t)wave + kCellWaves - turn) % kCellWaves;
+                turn = (turn + ngroups) % kCellWaves;
+                // the records of this wave's next group are loaded while the
+                // current group's taps are (indices clamped into the chunk)
+                RecMeta mnext[B];
+                auto load_meta = [&](const uint32_t g) {
+#pragma unroll
+                    for (int bi = 0; bi < B; ++bi)
+                        mnext[bi] = smeta[min(ch.start + g * B + (uint32_t)bi, rend - 1)];
+                };
+                load_meta(gfirst);
+                for (uint32_t gi = gfirst; gi < ngroups; gi += kCellWaves) {
+                    const uint32_t r0 = ch.start + gi * B;
+                    const uint32_t nb = min((uint32_t)B, rend - r0);
+                    // destination of this lane's sum (read now, used after the
+                    // reduction)
+                    const uint32_t dst = sperm[r0 + min((uint32_t)(my_idx >> 3), nb - 1)];
+                    float part[NV];
+#pragma unroll
+                    for (int i = 0; i < NV; ++i) part[i] = 0.0f;
+                    // every tap of the group's records loaded, then the
+                    // multiply-adds
+                    float2 w[B][NT];
+                    float4 ga[B][NT], gb[B][NT];
+#pragma unroll
+                    for (int bi = 0; bi < B; ++bi) {
+                        const RecMeta m = mnext[bi];
+                        const int sg = 2 * (((int)meta_kv(m) - cv0) * PITCH + ((int)meta_ku(m) - cu0));
+                        const char *tb, *tbv = nullptr;
+                        if constexpr (SEP) {
+                            tb = tbase + (size_t)(m.toff & 0xffffu) * kElem;
+                            tbv = tbase + (size_t)(m.toff >> 16) * kElem;
+                        } else {
+                            tb = tbase + (size_t)m.toff * kElem;
+                        }
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            uint32_t o = lt[t], ov = ltv[t];
+                            asm volatile("" : "+v"(o));   // keeps the offset 32-bit: scalar-base load
+                            if constexpr (SEP) {
+                                asm volatile("" : "+v"(ov));
+                                w[bi][t] = make_float2(
+                                    TapTraits<TapT>::real((const TapT *)(tb + o), 0) *
+                                        TapTraits<TapT>::real((const TapT *)(tbv + ov), 0),
+                                    0.0f);
+                            } else {
+                                w[bi][t] = TapTraits<TapT>::cplx((const TapT *)(tb + o), 0);
+                            }
+                            ga[bi][t] = cells[sg + lg[t]];
+                            gb[bi][t] = cells[sg + lg[t] + 1];
+                        }
+                    }
+                    load_meta(gi + kCellWaves);
+#pragma unroll
+                    for (int bi = 0; bi < B; ++bi) {
+                        // lanes past S^2 in the last tap contribute nothing
+                        if (!last_full && !last_on) {
+                            w[bi][NT - 1] = make_float2(0.0f, 0.0f);
+                            ga[bi][NT - 1] = gb[bi][NT - 1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                        }
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            // record bi's sums += conj(w) G
+                            const float4 a4 = ga[bi][t], b4 = gb[bi][t];
+                            const float gr[4] = {a4.x, b4.x, a4.y, b4.y};
+                            const float gim[4] = {a4.z, b4.z, a4.w, b4.w};
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                float &ar = part[bi * 8 + 2 * q];
+                                float &ai = part[bi * 8 + 2 * q + 1];
+                                if constexpr (SEP) {
+                                    ar = fmaf(w[bi][t].x, gr[q], ar);
+                                    ai = fmaf(w[bi][t].x, gim[q], ai);
+                                } else {
+                                    ar = fmaf(w[bi][t].x, gr[q], fmaf(w[bi][t].y, gim[q], ar));
+                                    ai = fmaf(w[bi][t].x, gim[q], fmaf(-w[bi][t].y, gr[q], ai));
+                                }
+                            }
+                        }
+                    }
+                    wave_reduce_scatter<NV>(part, lane);
+                    if (writer) {
+                        const int bi = my_idx >> 3, q = my_idx & 7;
+                        if ((uint32_t)bi < nb && (q >> 1) < npol)
+                            vis_out[((size_t)dst * npol + (q >> 1)) * 2 + (q & 1)] = part[0];
+                    }
+                }
+            };
+            if (in_lds) {
+                by_cell();
+            } else {
+                switch ((S * S + 63) >> 6) {
+                case 1: by_tap(std::integral_constant<int, 1>{}); break;
+                case 2: by_tap(std::integral_constant<int, (NTAP < 2 ? NTAP : 2)>{}); break;
+                case 3: by_tap(std::integral_constant<int, (NTAP < 3 ? NTAP : 3)>{}); break;
+                default: by_tap(std::integral_constant<int, NTAP>{}); break;
+                }
+            }
+        }
+    }
+}
+
+// Supports 17 to 32: the lanes of a wave take the taps of one record (tap
 // q = t * 64 + lane, q < S^2), so no lane sits outside a footprint.  A
 // workgroup takes a unit (chunks of one tile over the planes of the group);
 // the unit's grid region is staged once in LDS as [row][pol][col] float2
@@ -345,12 +746,9 @@ __global__ __launch_bounds__(NW * kWave) void degrid_block_kernel(
 template <int PITCH>
 constexpr int row_stride() { return 4 * PITCH + 8; }
 
-// Waves per workgroup of the taps kernel: the S <= 8 and S <= 32 instances
-// share each staged region among eight waves, which doubles the waves a CU
-// holds where the region's LDS (S <= 32) or the workgroup count (S <= 8)
-// limits them; the S <= 16 instance is held to four waves per SIMD by its
-// registers either way.
-constexpr int taps_waves(int ntap) { return ntap == 4 ? 4 : 8; }
+// Waves per workgroup of the taps kernel: eight share each staged region, whose
+// LDS limits how many workgroups a CU holds.
+constexpr int taps_waves(int) { return 8; }
 
 template <int NTAP, int PITCH, int B, bool SEP, typename TapT>
 __global__ __launch_bounds__(kWave * taps_waves(NTAP)) void degrid_taps_kernel(
@@ -446,11 +844,10 @@ __global__ __launch_bounds__(kWave * taps_waves(NTAP)) void degrid_taps_kernel(
             const int nt_rt = (S * S + 63) >> 6;
             const bool last_full = (S * S) % 64 == 0;
             const bool last_on = ((nt_rt - 1) * 64 + lane) < S * S;
-            // NT: taps held per lane; a compile-time count (one instance per
-            // count) for up to 4 taps, else NTAP with the count tested
-            auto run = [&](auto nt_t) {
-                constexpr int NT = decltype(nt_t)::value;
-                const int nt = (NTAP <= 4) ? NT : nt_rt;
+            // NTAP taps held per lane, the chunk's count tested
+            auto run = [&]() {
+                constexpr int NT = NTAP;
+                const int nt = nt_rt;
                 int lg[NT];
                 uint32_t lt[NT], ltv[NT];
 #pragma unroll
@@ -467,8 +864,8 @@ __global__ __launch_bounds__(kWave * taps_waves(NTAP)) void degrid_taps_kernel(
                         ltv[t] = 0u;
                     }
                 }
-                // the last tap's offsets (its index is a run-time value for
-                // NTAP > 4: picked once per chunk)
+                // the last tap's offsets (its index is a run-time value: picked
+                // once per chunk)
                 int lg_last = lg[0];
                 uint32_t lt_last = lt[0], ltv_last = ltv[0];
 #pragma unroll
@@ -556,46 +953,29 @@ __global__ __launch_bounds__(kWave * taps_waves(NTAP)) void degrid_taps_kernel(
                             ai = fmaf(w.x, gv[q].y, fmaf(-w.y, gv[q].x, ai));
                         }
                     };
-                    if constexpr (NTAP > 4) {
 #pragma unroll
-                        for (int bi = 0; bi < B; ++bi) {
-                            // many taps per lane: four at a time (their loads
-                            // in flight together; the LDS region already
-                            // limits the kernel to two waves per SIMD, so the
-                            // registers are there)
+                    for (int bi = 0; bi < B; ++bi) {
+                        // many taps per lane: four at a time (their loads
+                        // in flight together; the LDS region already
+                        // limits the kernel to two waves per SIMD, so the
+                        // registers are there)
 #pragma unroll
-                            for (int t = 0; t < NT - 1; t += 4) {
-                                if (t < nt - 1) {
-                                    float2 w[4], gv[4][4];
+                        for (int t = 0; t < NT - 1; t += 4) {
+                            if (t < nt - 1) {
+                                float2 w[4], gv[4][4];
 #pragma unroll
-                                    for (int u = 0; u < 4; ++u)
-                                        if (t + u < NT - 1 && t + u < nt - 1)
-                                            load(bi, lg[t + u], lt[t + u], ltv[t + u], w[u], gv[u]);
+                                for (int u = 0; u < 4; ++u)
+                                    if (t + u < NT - 1 && t + u < nt - 1)
+                                        load(bi, lg[t + u], lt[t + u], ltv[t + u], w[u], gv[u]);
 #pragma unroll
-                                    for (int u = 0; u < 4; ++u)
-                                        if (t + u < NT - 1 && t + u < nt - 1) fma4(bi, w[u], gv[u]);
-                                }
+                                for (int u = 0; u < 4; ++u)
+                                    if (t + u < NT - 1 && t + u < nt - 1) fma4(bi, w[u], gv[u]);
                             }
-                            float2 w, gv[4];
-                            load(bi, lg_last, lt_last, ltv_last, w, gv);
-                            if (!last_full) mask_last(w, gv);
-                            fma4(bi, w, gv);
                         }
-                    } else {
-                        // every tap of the group's records loaded, then the
-                        // multiply-adds
-                        float2 w[B][NT], gv[B][NT][4];
-#pragma unroll
-                        for (int bi = 0; bi < B; ++bi)
-#pragma unroll
-                            for (int t = 0; t < NT; ++t)
-                                load(bi, lg[t], lt[t], ltv[t], w[bi][t], gv[bi][t]);
-#pragma unroll
-                        for (int bi = 0; bi < B; ++bi) {
-                            if (!last_full) mask_last(w[bi][NT - 1], gv[bi][NT - 1]);
-#pragma unroll
-                            for (int t = 0; t < NT; ++t) fma4(bi, w[bi][t], gv[bi][t]);
-                        }
+                        float2 w, gv[4];
+                        load(bi, lg_last, lt_last, ltv_last, w, gv);
+                        if (!last_full) mask_last(w, gv);
+                        fma4(bi, w, gv);
                     }
                     wave_reduce_scatter<NV>(part, lane);
                     if (writer) {
@@ -605,16 +985,7 @@ __global__ __launch_bounds__(kWave * taps_waves(NTAP)) void degrid_taps_kernel(
                     }
                 }
             };
-            if constexpr (NTAP <= 4) {
-                switch (nt_rt) {
-                case 1: run(std::integral_constant<int, 1>{}); break;
-                case 2: run(std::integral_constant<int, (NTAP < 2 ? NTAP : 2)>{}); break;
-                case 3: run(std::integral_constant<int, (NTAP < 3 ? NTAP : 3)>{}); break;
-                default: run(std::integral_constant<int, NTAP>{}); break;
-                }
-            } else {
-                run(std::integral_constant<int, NTAP>{});
-            }
+            run();
         }
     }
 }
@@ -683,12 +1054,40 @@ hipError_t launch_dt(const DegridPtrs &a, const DegridParams &prm, int tile, int
     return hipGetLastError();
 }
 
+// The cells kernel, with LDS for the largest tap table of the launch's planes
+// that fits beside the region with two workgroups to a CU.
+template <int NTAP, bool SEP, typename TapT>
+hipError_t launch_dc(const DegridPtrs &a, DegridParams prm, int tile, int smax,
+                     const PlaneLayout *planes, hipStream_t stream) {
+    if (tile != kCellTile || smax > cells_smax(NTAP)) return hipErrorInvalidValue;
+    size_t table = 0;
+    for (int p = prm.p_lo; p < prm.p_hi; ++p) {
+        const size_t w = (size_t)prm.beta * planes[p].S;
+        const size_t t = w * w * (SEP ? sizeof(float) : 2 * sizeof(TapT));
+        if (cells_region(NTAP) + t <= kCellLds) table = std::max(table, t);
+    }
+    table = (table + 7) & ~size_t(7);
+    prm.tab_bytes = (uint32_t)table;
+    // (16 cells past a table's end are read, and count as zero)
+    const size_t lds = cells_region(NTAP) + table + (table ? 16 * 2 * sizeof(float) : 0);
+    // records per reduction group of the lane-per-tap path: two where a lane
+    // holds several taps (registers; the reduction costs about the same per
+    // record either way)
+    auto kern = degrid_cells_kernel<NTAP, (NTAP > 1 ? 2 : 4), SEP, TapT>;
+    constexpr int threads = kWave * kCellWaves;
+    hipLaunchKernelGGL(kern, dim3(resident_groups((const void *)kern, threads, lds)),
+                       dim3(threads), lds, stream, a.smeta, a.sperm, a.grid, a.vis_out,
+                       (const TapT *)a.taps, a.chunks, a.bucket_cfirst, a.units, a.group_nunits,
+                       a.planes, a.queue, prm);
+    return hipGetLastError();
+}
+
 template <bool SEP, typename TapT>
 hipError_t launch_deg(int cls, const DegridPtrs &a, const DegridParams &prm, int tile, int smax,
-                      hipStream_t stream) {
+                      const PlaneLayout *planes, hipStream_t stream) {
     switch (cls) {
-    case 0: return launch_dt<1, 32, SEP, TapT>(a, prm, tile, smax, stream);
-    case 1: return launch_dt<4, 32, SEP, TapT>(a, prm, tile, smax, stream);
+    case 0: return launch_dc<1, SEP, TapT>(a, prm, tile, smax, planes, stream);
+    case 1: return launch_dc<4, SEP, TapT>(a, prm, tile, smax, planes, stream);
     case 2: return launch_dt<16, 48, SEP, TapT>(a, prm, tile, smax, stream);
     default: return launch_dg<7, 16, 2, SEP, TapT>(a, prm, tile, smax, stream);
     }
@@ -696,11 +1095,11 @@ hipError_t launch_deg(int cls, const DegridPtrs &a, const DegridParams &prm, int
 
 template <bool SEP>
 hipError_t launch_deg_t(mg_dtype dt, int cls, const DegridPtrs &a, const DegridParams &prm,
-                        int tile, int smax, hipStream_t stream) {
+                        int tile, int smax, const PlaneLayout *planes, hipStream_t stream) {
     switch (dt) {
-    case MG_F16: return launch_deg<SEP, __half>(cls, a, prm, tile, smax, stream);
-    case MG_BF16: return launch_deg<SEP, __hip_bfloat16>(cls, a, prm, tile, smax, stream);
-    default: return launch_deg<SEP, float>(cls, a, prm, tile, smax, stream);
+    case MG_F16: return launch_deg<SEP, __half>(cls, a, prm, tile, smax, planes, stream);
+    case MG_BF16: return launch_deg<SEP, __hip_bfloat16>(cls, a, prm, tile, smax, planes, stream);
+    default: return launch_deg<SEP, float>(cls, a, prm, tile, smax, planes, stream);
     }
 }
 
@@ -730,7 +1129,8 @@ mg_status launch_degrid(const PlanState &P, const void *grid, void *vis_out, voi
     DegridPtrs a{P.smeta,    P.sperm,         (const float *)grid, (float *)vis_out,
                  P.taps,     P.chunks,        P.bucket_cfirst,     P.units,
                  P.group_nunits, P.d_planes,  nullptr};
-    DegridParams prm{P.geom.npol, P.geom.nu, P.geom.nv, P.geom.beta, 0, 0};
+    DegridParams prm{P.geom.npol, P.geom.nu, P.geom.nv, P.geom.beta, 0, 0,
+                     (uint32_t)P.geom.conj_base, 0};
     const bool sep = P.kind == MG_KERNEL_SEPARABLE;
     // one launch per run of consecutive planes of the same class
     int p0 = 0;
@@ -745,8 +1145,10 @@ mg_status launch_degrid(const PlanState &P, const void *grid, void *vis_out, voi
         prm.p_hi = p1;
         a.queue = queues + p0;
         const int cls = P.planes[p0].cls;
-        e = sep ? launch_deg_t<true>(P.tap_dtype, cls, a, prm, P.planes[p0].T, smax, stream)
-                : launch_deg_t<false>(P.tap_dtype, cls, a, prm, P.planes[p0].T, smax, stream);
+        e = sep ? launch_deg_t<true>(P.tap_dtype, cls, a, prm, P.planes[p0].T, smax,
+                                     P.planes.data(), stream)
+                : launch_deg_t<false>(P.tap_dtype, cls, a, prm, P.planes[p0].T, smax,
+                                      P.planes.data(), stream);
         p0 = p1;
     }
     if (e == hipSuccess) e = hipGetLastError();
