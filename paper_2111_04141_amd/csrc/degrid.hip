@@ -377,6 +377,11 @@ constexpr size_t kCellLds = 80 * 1024 - 256;
 // Records per oversampling phase a chunk needs for its plane's table to be
 // copied to LDS (as the window gridders': the copy reads the table once).
 constexpr uint32_t kCellStagePerPhase = 16;
+// Records per cell of its bounding box a chunk needs to be taken by cell: a
+// group of one record costs half as much again as on the lane-per-tap path.
+// 3.0M records of a bf16 bank, S <= 16, 2.6 records a cell: 264 us with two, 297
+// without the rule.
+constexpr uint32_t kDensePerCell = 2;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -471,26 +476,16 @@ __attribute__((amdgpu_waves_per_eu(4))) void degrid_cells_kernel(
             const int S = planes[pc].S;
             const uint32_t tap_off = planes[pc].tap_off;
             const uint32_t ntap = beta * beta * (uint32_t)(S * S);   // phase-major S x S blocks
+            // dense enough to be taken by cell
+            const uint32_t box = (((ch.bbox >> 8) & 0xffu) - (ch.bbox & 0xffu) + 1u) *
+                                 ((ch.bbox >> 24) - ((ch.bbox >> 16) & 0xffu) + 1u);
+            const bool dense = ch.len >= kDensePerCell * box;
             bool in_lds = staged == pc;
-            if (!in_lds && (gl.grp_n == 1 || ch.len >= kCellStagePerPhase * beta * beta) &&
+            if (!in_lds && dense &&
+                (gl.grp_n == 1 || ch.len >= kCellStagePerPhase * beta * beta) &&
                 ntap * kElemLds <= prm.tab_bytes) {
                 __syncthreads();   // the previous table's readers are done
-                if constexpr (SEP) {
-                    float *t = reinterpret_cast<float *>(s_tab);
-                    for (uint32_t e = threadIdx.x; e < ntap; e += kThreads) {
-                        const uint32_t blk = e / (uint32_t)(S * S), r = e - blk * (uint32_t)(S * S);
-                        const uint32_t j = r / (uint32_t)S, i = r - j * (uint32_t)S;
-                        const uint32_t ov = blk / beta, ou = blk - ov * beta;
-                        t[e] = TapTraits<TapT>::real(taps, ou * (uint32_t)S + i) *
-                               TapTraits<TapT>::real(taps, ov * (uint32_t)S + j);
-                    }
-                } else {
-                    const uint32_t *src =
-                        reinterpret_cast<const uint32_t *>(tbase + (size_t)tap_off * kElem);
-                    uint32_t *t = reinterpret_cast<uint32_t *>(s_tab);
-                    for (uint32_t e = threadIdx.x; e < ntap * (kElem / 4); e += kThreads)
-                        t[e] = src[e];
-                }
+                stage_taps<SEP, TapT>(s_tab, taps, tap_off, (uint32_t)S, beta, kThreads);
                 __syncthreads();
                 staged = pc;
                 in_lds = true;
@@ -721,7 +716,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void degrid_cells_kernel(
                     }
                 }
             };
-            if (in_lds) {
+            if (in_lds && dense) {
                 by_cell();
             } else {
                 switch ((S * S + 63) >> 6) {

@@ -198,7 +198,7 @@ constexpr size_t kWindowLds = 80 * 1024;
 // the chunk.
 // A group of one plane copies its table once per workgroup whatever the chunk:
 // 100,800 records on 1024^2, in chunks of 64: 67 us in place of 71.
-constexpr uint32_t kStagePerPhase = 16;
+constexpr uint32_t kStagePerPhase = 8;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -324,22 +324,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void grid_window_kernel(
             bool in_lds = staged == pc;
             if (!in_lds && ch.len >= kStagePerPhase * beta * beta && ntap * kElemLds <= prm.tab_bytes) {
                 __syncthreads();   // the previous table's readers are done
-                if constexpr (SEP) {
-                    float *t = reinterpret_cast<float *>(s_tab);
-                    for (uint32_t e = threadIdx.x; e < ntap; e += NW * kWave) {
-                        const uint32_t blk = e / (uint32_t)(S * S), r = e - blk * (uint32_t)(S * S);
-                        const uint32_t j = r / (uint32_t)S, i = r - j * (uint32_t)S;
-                        const uint32_t ov = blk / beta, ou = blk - ov * beta;
-                        t[e] = TapTraits<TapT>::real(taps, ou * (uint32_t)S + i) *
-                               TapTraits<TapT>::real(taps, ov * (uint32_t)S + j);
-                    }
-                } else {
-                    const uint32_t *src = reinterpret_cast<const uint32_t *>(
-                        tbase + (size_t)tap_off * kElem);
-                    uint32_t *t = reinterpret_cast<uint32_t *>(s_tab);
-                    for (uint32_t e = threadIdx.x; e < ntap * (kElem / 4); e += NW * kWave)
-                        t[e] = src[e];
-                }
+                stage_taps<SEP, TapT>(s_tab, taps, tap_off, (uint32_t)S, beta, NW * kWave);
                 __syncthreads();
                 staged = pc;
                 in_lds = true;

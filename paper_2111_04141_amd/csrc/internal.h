@@ -92,6 +92,48 @@ struct GridScratch {
     uint32_t *queues = nullptr;  // [nplanes_eff]
 };
 
+// Copies a plane's phase-major tap table into LDS, `threads` threads together
+// (the caller synchronises): W-projection the table's words, separable the
+// S x S products of every phase's taps.  Eight loads in flight a thread: one at
+// a time the copy is a chain of load latencies, 16 for a 33 KB table.
+template <bool SEP, typename TapT>
+__device__ inline void stage_taps(char *lds, const TapT *__restrict__ taps, uint32_t tap_off,
+                                  uint32_t S, uint32_t beta, uint32_t threads) {
+    constexpr int kAhead = 8;
+    const uint32_t ntap = beta * beta * S * S;
+    if constexpr (SEP) {
+        float *t = reinterpret_cast<float *>(lds);
+        for (uint32_t e0 = threadIdx.x; e0 < ntap; e0 += kAhead * threads) {
+            float a[kAhead], b[kAhead];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                const uint32_t e = min(e0 + k * threads, ntap - 1);
+                const uint32_t blk = e / (S * S), r = e - blk * (S * S);
+                const uint32_t j = r / S, i = r - j * S;
+                const uint32_t ov = blk / beta, ou = blk - ov * beta;
+                a[k] = TapTraits<TapT>::real(taps, ou * S + i);
+                b[k] = TapTraits<TapT>::real(taps, ov * S + j);
+            }
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k)
+                if (e0 + k * threads < ntap) t[e0 + k * threads] = a[k] * b[k];
+        }
+    } else {
+        constexpr uint32_t kWords = 2 * sizeof(TapT) / 4;   // words per tap
+        const uint32_t n = ntap * kWords;
+        const uint32_t *src = reinterpret_cast<const uint32_t *>(taps) + (size_t)tap_off * kWords;
+        uint32_t *t = reinterpret_cast<uint32_t *>(lds);
+        for (uint32_t e0 = threadIdx.x; e0 < n; e0 += kAhead * threads) {
+            uint32_t x[kAhead];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) x[k] = src[min(e0 + k * threads, n - 1)];
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k)
+                if (e0 + k * threads < n) t[e0 + k * threads] = x[k];
+        }
+    }
+}
+
 // Errors (thread-local message).
 mg_status set_error(mg_status s, const std::string &msg);
 
