@@ -245,8 +245,9 @@ __device__ inline void add_screened(float2 &sum, float2 v, double w, double nm1)
 // Power-of-two sides: the columns of every layer transformed, screened and
 // summed in registers, so the transformed layers never reach HBM.  Held to 128
 // VGPRs (two workgroups of 512 threads to a CU): 64 transforms of 2048 x 2048
-// take 0.88 ms, 1.33 ms with the registers it would take; the layers' one read
-// takes 0.42 ms at a device copy's rate.
+// take 1.07 ms (0.88, against 1.33 with the registers it would take, before the
+// twiddles were formed in FP64); the layers' one read takes 0.42 ms at a device
+// copy's rate.
 template <int LOGN>
 __global__ __launch_bounds__(fft_col_threads(LOGN)) __attribute__((amdgpu_waves_per_eu(4)))
 void wstack_columns_kernel(
