@@ -50,8 +50,8 @@ PAPER_P100 = ("Conv Gridder FP32 Npol=4 max 3.62 GRecs/s x 36 = 1.30e11 updates/
 # call's dispatches and scaled by the reading of a plain device copy of known
 # size.  Valid only for the kernel sources with this digest; any change to
 # them makes the figure stale and it is then reported as null.
-MEASURED_TRAFFIC = {"sources": "9521dc875ade642d", "bytes_per_call": 32.57e9,
-                    "read_bytes": 16.95e9, "written_bytes": 15.62e9,
+MEASURED_TRAFFIC = {"sources": "e56114d6a39fc8b8", "bytes_per_call": 21.65e9,
+                    "read_bytes": 11.57e9, "written_bytes": 10.08e9,
                     "profile": "profiles/grid_wproj8192_134M_hbm_traffic.txt"}
 TRAFFIC_SOURCES = ("grid.hip", "plan.hip", "api.hip", "common.h", "internal.h")
 
@@ -334,10 +334,9 @@ def precision_leg(api, W, torch, dev, stream, steps):
 
 def imaging_leg(api, W, torch, dev, stream, wl, name):
     """The imaging chain on a convolutional grid of the workload: corrector
-    vector, origin shifts fused around the platform library's batched C2C
-    inverse FFT (one per polarisation) and the separable correction.  The
-    fused shift-in and correct-out kernels stream the grid twice (read and
-    write, 4 x 8 bytes per cell each); the FFT is the library's."""
+    vector, then a row and a column transform with the origin shifts, the
+    separable correction and the crop fused in (4 x 8 bytes per cell read and
+    written by each)."""
     import numpy as np
     timer = Timer(torch, stream)
     n = wl.n
@@ -351,12 +350,12 @@ def imaging_leg(api, W, torch, dev, stream, wl, name):
     corr = timer.protocol(lambda: api.corrector(n, wl.beta, t, wl.beta))
     im.close()
     grid_bytes = 4 * 8 * n * n
-    # the least traffic of the chain: shift-in, one FFT pass and the
-    # correction each read and write the grid once
+    # the traffic of the chain: the row and the column pass each read and
+    # write the grid once
     r = {"workload": name, "grid": [4, n, n], "chain": chain, "library_fft_alone": fft,
          "corrector": corr,
-         "chain_hbm_frac": 6 * grid_bytes / (HBM_PEAK_GBS * 1e9) / (chain["mean_ms"] * 1e-3),
-         "note": "chain_hbm_frac: 6 x the grid bytes (three read-write passes) over the chain "
+         "chain_hbm_frac": 4 * grid_bytes / (HBM_PEAK_GBS * 1e9) / (chain["mean_ms"] * 1e-3),
+         "note": "chain_hbm_frac: 4 x the grid bytes (two read-write passes) over the chain "
                  "time; torch.fft.ifft2 of the same grid timed alone for comparison"}
     log(f"[bench] imaging {name}: chain {chain['mean_ms']:.3f} ms, library FFT alone "
         f"{fft['mean_ms']:.3f} ms, corrector {corr['mean_ms']:.4f} ms")
@@ -366,12 +365,12 @@ def imaging_leg(api, W, torch, dev, stream, wl, name):
 def kernel_bank_leg(api, W, torch, dev, wl_wproj):
     """The W-projection bank of the 32-plane schedule (S 8 -> 64,
     oversampling 4, the W-projection and precision workloads' bank), built
-    on the device in FP64 (taper, screen, batched Z2Z FFT per plane size,
-    normalisation); the FP64 oracle's time for the same bank is part of the
-    CPU baseline.  Timed on the host clock around a synchronised call (it
-    includes the workspace allocation and about 160 launches), after a first
-    call that creates the FFT plans; the FFT flops use 5 M^2 log2(M^2) per
-    M x M plane."""
+    on the device in FP64 (taper, screen, cosine transforms of the kept
+    samples as matrix products, normalisation); the FP64 oracle's time for the
+    same bank is part of the CPU baseline.  Timed on the host clock around a
+    synchronised call (it includes the workspace allocation and five
+    launches), after a first call; the flops are those of an FFT of each
+    M x M plane, 5 M^2 log2(M^2), which the builder does not need."""
     import numpy as np
     b = wl_wproj.bank
     sup = [int(x) for x in b.supports]
@@ -379,7 +378,7 @@ def kernel_bank_leg(api, W, torch, dev, wl_wproj):
     ws = [p * dw for p in range(len(sup))]
     base = W.pswf_taps(7, 4)
     bt = torch.from_numpy(base).to(dev)
-    api.wkernel_bank(sup, ws, 4, bt, wl_wproj.scale)          # FFT plans made
+    api.wkernel_bank(sup, ws, 4, bt, wl_wproj.scale)
     torch.cuda.synchronize()
     times = []
     for _ in range(5):
@@ -393,7 +392,7 @@ def kernel_bank_leg(api, W, torch, dev, wl_wproj):
          "device_ms_min": float(min(times)), "device_ms_median": float(np.median(times)),
          "fft_flops": flops,
          "fft_fp64_frac_at_min": flops / (FP64_PEAK_TFLOPS * 1e12) / (min(times) * 1e-3),
-         "note": "launch-bound at this size: the whole bank is 32 planes of at most 512^2 "
+         "note": "latency-bound at this size: the whole bank is 32 planes of at most 512^2 "
                  "points"}
     log(f"[bench] kernel bank: device {min(times):.2f} ms (median {np.median(times):.2f})")
     return r
@@ -402,9 +401,9 @@ def kernel_bank_leg(api, W, torch, dev, wl_wproj):
 def wstack_leg(api, W, torch, dev, stream, wl, name, layers=16):
     """W-stacking on the workload's records: gridding onto `layers` layer
     grids (the plain gridder's kernels on the stacked grid) against gridding
-    the same records onto one grid, and the W-stacking image (batched FFT of
-    every layer and polarisation, screen-and-sum kernel that reads every
-    layer once and writes the image)."""
+    the same records onto one grid, and the W-stacking image (row transforms of
+    every layer and polarisation, then column transforms with the screens and
+    the sum over layers fused in, which write only the image)."""
     import numpy as np
     timer = Timer(torch, stream)
     n = wl.n
@@ -439,11 +438,11 @@ def wstack_leg(api, W, torch, dev, stream, wl, name, layers=16):
          "wstack_grid_updates_per_s": upd / (tw["mean_ms"] * 1e-3),
          "wstack_over_plain_grid_time": tw["mean_ms"] / tp["mean_ms"],
          "image": ti, "library_fft_alone": fft,
-         "image_hbm_frac": (5 * layer_bytes + 4 * 8 * n * n) / (HBM_PEAK_GBS * 1e9)
+         "image_hbm_frac": (3 * layer_bytes + 4 * 8 * n * n) / (HBM_PEAK_GBS * 1e9)
                            / (ti["mean_ms"] * 1e-3),
-         "note": "image_hbm_frac: the least traffic of the chain (shift-in and one FFT pass "
-                 "read and write every layer, the screen-and-sum reads every layer and writes "
-                 "the image) over the image time"}
+         "note": "image_hbm_frac: the traffic of the chain (the row pass reads and writes every "
+                 "layer, the column pass reads every layer and writes the image) over the "
+                 "image time"}
     log(f"[bench] wstack {name}: {layers} layers, grid {tw['mean_ms']:.3f} ms (plain "
         f"{tp['mean_ms']:.3f} ms), image {ti['mean_ms']:.3f} ms (FFT alone {fft['mean_ms']:.3f})")
     return r

@@ -35,10 +35,10 @@
 // for the sparse planes of large |w|; see the kernel's comment.
 //
 // All polarisations are handled per visit: one tap load feeds 4 complex
-// multiply-adds (the thesis's Polarisation Gain, Section 3.5).  Records are
-// read on the scalar unit (visibilities become SGPR operands of the FMAs),
-// and each carries the table offset of its first tap (in the conjugated copy
-// of the bank for w < 0), so the per-record scalar work is small.
+// multiply-adds (the thesis's Polarisation Gain, Section 3.5), on the matrix
+// cores in the window kernel, on the vector units in the block kernel, which
+// reads its records on the scalar unit.  Each record carries the table offset
+// of its first tap (in the conjugated copy of the bank for w < 0).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
