@@ -11,8 +11,8 @@
 //    every column and applies the signs, the correctors and the crop as it
 //    stores: the grid crosses HBM twice each way.  The platform library's 2-D
 //    transform alone takes two row passes and two transpositions.  4 x 2048 x
-//    2048: rows 47 us (at a device copy's rate), columns 60 us; with the
-//    library's transform between two kernels of its own the chain took 277 us.
+//    2048: rows 51 us (near a device copy's rate), columns 63 us, 124 us in all;
+//    with the library's transform between two kernels of its own 280 us.
 //  * Other even sides: the platform library's batched C2C transform, out of
 //    place, and one kernel for the shift, signs, correctors and crop (where the
 //    image is to take the scratch's place, the signs go in first instead).
