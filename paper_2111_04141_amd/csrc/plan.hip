@@ -362,7 +362,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(DevGeom g,
 // and commit the tile's region once per unit rather than once per chunk.  units[first chunk of the group + k] = (first chunk, chunk count)
 // of the group's unit k; group_nunits[g] = unit count (cleared beforehand).
 // A wave's units are consecutive and in tile order.
-// One launch covers every group (blockIdx.y).
+// One launch covers every group (blockIdx.y) and every tile (a thread each).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void unit_list_kernel(const PlaneLayout *__restrict__ planes,
                                                         GroupList groups,
@@ -783,9 +783,12 @@ mg_status plan_build(PlanState &P, const void *taps, const void *uvw, mg_dtype u
     // units of every plane group
     GroupList groups{};
     const int ngroups = plane_groups(P.planes, groups);
-    const int64_t tiles = (int64_t)P.planes[0].ntu * P.planes[0].ntv;   // (T is every plane's)
-    hipLaunchKernelGGL(unit_list_kernel, dim3(grid_blocks(tiles, 256), ngroups), dim3(256), 0,
-                       stream, P.d_planes, groups, P.bucket_cfirst, P.chunks, R, P.units,
+    // (a thread per tile and no stride loop: the wave's prefix sum takes every
+    // tile once, so the launch has to cover them all, up to 65536 workgroups)
+    int64_t tiles = 1;
+    for (const PlaneLayout &L : P.planes) tiles = std::max(tiles, (int64_t)L.ntu * L.ntv);
+    hipLaunchKernelGGL(unit_list_kernel, dim3((unsigned)((tiles + 255) / 256), ngroups), dim3(256),
+                       0, stream, P.d_planes, groups, P.bucket_cfirst, P.chunks, R, P.units,
                        P.group_nunits);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(MG_EDEVICE, std::string("plan kernels: ") + hipGetErrorString(e));
