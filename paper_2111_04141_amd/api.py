@@ -148,6 +148,19 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+def _is_lazy(t: torch.Tensor) -> bool:
+    """A conjugate or negative view: its memory does not hold its values (refused
+    as an output)."""
+    return t.is_conj() or t.is_neg()
+
+
+def _stored(t: torch.Tensor) -> torch.Tensor:
+    """An input as its memory has to hold it: the library reads raw pointers, so a
+    lazily conjugated or negated tensor is materialised.  (Others are returned as
+    they are, strided ones for the call's own check to refuse.)"""
+    return t.resolve_conj().resolve_neg() if _is_lazy(t) and t.is_contiguous() else t
+
+
 # ---------------------------------------------------------------------------
 # descriptors
 # ---------------------------------------------------------------------------
@@ -185,7 +198,7 @@ class KernelBank:
             raise ValueError("kind must be 'separable', 'wproj' or 'wstack'")
         if not taps.is_cuda:
             raise ValueError("taps must be a device tensor")
-        taps = taps.contiguous()
+        taps = _stored(taps.contiguous())
         if kind == "wproj":
             if taps.dtype == torch.complex64:
                 tdt, nt = MG_F32, taps.numel()
@@ -240,7 +253,7 @@ def _check_uvw(uvw: torch.Tensor) -> int:
 
 def _check_vis(vis: torch.Tensor, nrec: int, npol: int):
     if (not vis.is_cuda or vis.dtype != torch.complex64 or not vis.is_contiguous()
-            or tuple(vis.shape) != (nrec, npol)):
+            or _is_lazy(vis) or tuple(vis.shape) != (nrec, npol)):
         raise ValueError(f"vis must be a contiguous complex64 [{nrec}, {npol}] device tensor")
 
 
@@ -255,7 +268,7 @@ def grid_shape(spec: GridSpec, bank: Optional["KernelBank"] = None) -> tuple:
 def _check_grid(g: torch.Tensor, spec: GridSpec, bank: Optional["KernelBank"] = None):
     shape = grid_shape(spec, bank)
     if (not g.is_cuda or g.dtype != torch.complex64 or not g.is_contiguous()
-            or tuple(g.shape) != shape):
+            or _is_lazy(g) or tuple(g.shape) != shape):
         raise ValueError(f"grid must be a contiguous complex64 {list(shape)} device tensor")
 
 
@@ -287,6 +300,7 @@ def grid(spec: GridSpec, bank: KernelBank, uvw: torch.Tensor, vis: torch.Tensor,
     """One-shot gridding (index + sort + grid): out += G vis."""
     dt = _check_uvw(uvw)
     n = uvw.shape[0]
+    vis = _stored(vis)
     _check_vis(vis, n, spec.npol)
     if out is None:
         out = torch.zeros(grid_shape(spec, bank), dtype=torch.complex64, device=uvw.device)
@@ -304,6 +318,7 @@ def grid_static(spec: GridSpec, bank: KernelBank, uvw: torch.Tensor, vis: torch.
     calls on one GPU must not overlap): out += G vis."""
     dt = _check_uvw(uvw)
     n = uvw.shape[0]
+    vis = _stored(vis)
     _check_vis(vis, n, spec.npol)
     if out is None:
         out = torch.zeros(grid_shape(spec, bank), dtype=torch.complex64, device=uvw.device)
@@ -325,6 +340,7 @@ def degrid(spec: GridSpec, bank: KernelBank, uvw: torch.Tensor, grid_in: torch.T
     """One-shot degridding: returns vis = G^H grid (skipped records get 0)."""
     dt = _check_uvw(uvw)
     n = uvw.shape[0]
+    grid_in = _stored(grid_in)
     _check_grid(grid_in, spec, bank)
     if out is None:
         out = torch.empty(n, spec.npol, dtype=torch.complex64, device=uvw.device)
@@ -338,8 +354,10 @@ def degrid(spec: GridSpec, bank: KernelBank, uvw: torch.Tensor, grid_in: torch.T
 def residual_(obs: torch.Tensor, model: torch.Tensor) -> torch.Tensor:
     """model = obs - model in place (complex64); returns sum |obs - model|^2 as
     a float64 0-dim device tensor (mg_residual)."""
+    obs = _stored(obs)
     for t in (obs, model):
-        if not t.is_cuda or t.dtype != torch.complex64 or not t.is_contiguous():
+        if (not t.is_cuda or t.dtype != torch.complex64 or not t.is_contiguous()
+                or _is_lazy(t)):
             raise ValueError("obs and model must be contiguous complex64 device tensors")
     if obs.shape != model.shape or obs.device != model.device:
         raise ValueError("obs and model must have one shape and device")
@@ -369,6 +387,7 @@ class Server:
                grid_out: torch.Tensor) -> int:
         dt = _check_uvw(uvw)
         n = uvw.shape[0]
+        vis = _stored(vis)
         _check_vis(vis, n, spec.npol)
         _check_grid(grid_out, spec, bank)
         # inputs are produced on torch's current stream: the job's stream waits
@@ -447,6 +466,7 @@ class Plan:
                                     _stream_ptr(uvw.device)), "mg_plan_create")
 
     def grid(self, vis: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
+        vis = _stored(vis)
         _check_vis(vis, self.nrec, self.spec.npol)
         if out is None:
             out = torch.zeros(grid_shape(self.spec, self.bank), dtype=torch.complex64,
@@ -458,6 +478,7 @@ class Plan:
 
     def grid_scaled(self, vis: torch.Tensor, factor: torch.Tensor) -> torch.Tensor:
         """grid(factor vis) on a new grid, factor a float64 0-dim device tensor."""
+        vis = _stored(vis)
         _check_vis(vis, self.nrec, self.spec.npol)
         if not factor.is_cuda or factor.dtype != torch.float64 or factor.numel() != 1:
             raise ValueError("factor must be a float64 device scalar")
@@ -469,6 +490,7 @@ class Plan:
         return out
 
     def degrid(self, grid_in: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
+        grid_in = _stored(grid_in)
         _check_grid(grid_in, self.spec, self.bank)
         if out is None:
             out = torch.empty(self.nrec, self.spec.npol, dtype=torch.complex64,
@@ -516,7 +538,7 @@ class Plan:
 def _check_hybrid_grid(g: torch.Tensor, spec: GridSpec):
     shape = (spec.npol, spec.beta * spec.nv, spec.nu)
     if (not g.is_cuda or g.dtype != torch.complex64 or not g.is_contiguous()
-            or tuple(g.shape) != shape):
+            or _is_lazy(g) or tuple(g.shape) != shape):
         raise ValueError(f"hybrid grid must be a contiguous complex64 {list(shape)} device tensor")
 
 
@@ -525,6 +547,7 @@ def hybrid_grid(spec: GridSpec, bank: KernelBank, uvw: torch.Tensor, vis: torch.
     """One-shot Hybrid Gridding Step: out [npol, beta nv, nu] += G_hy vis."""
     dt = _check_uvw(uvw)
     n = uvw.shape[0]
+    vis = _stored(vis)
     _check_vis(vis, n, spec.npol)
     if out is None:
         out = torch.zeros(spec.npol, spec.beta * spec.nv, spec.nu, dtype=torch.complex64,
@@ -557,6 +580,7 @@ class HybridPlan:
                                            _stream_ptr(uvw.device)), "mg_hybrid_plan_create")
 
     def grid(self, vis: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.Tensor:
+        vis = _stored(vis)
         _check_vis(vis, self.nrec, self.spec.npol)
         if out is None:
             out = torch.zeros(self.spec.npol, self.spec.beta * self.spec.nv, self.spec.nu,
@@ -596,6 +620,7 @@ def prune_columns(grid_in: torch.Tensor, alpha: int, ztaps: torch.Tensor, suppor
     """Column pruning: every column of grid_in [npol, M, ncols] circularly
     convolved with the pruning kernel (FP32 device table of alpha Sz + 1
     values) and downsampled by alpha; returns [npol, M / alpha, ncols]."""
+    grid_in = _stored(grid_in)
     if (not grid_in.is_cuda or grid_in.dtype != torch.complex64 or not grid_in.is_contiguous()
             or grid_in.dim() != 3):
         raise ValueError("grid_in must be a contiguous complex64 [npol, M, ncols] device tensor")
@@ -605,7 +630,7 @@ def prune_columns(grid_in: torch.Tensor, alpha: int, ztaps: torch.Tensor, suppor
         raise ValueError("ztaps must be a contiguous float32 device tensor of alpha*Sz+1 values")
     if out is None:
         out = torch.empty(npol, M // alpha, ncols, dtype=torch.complex64, device=grid_in.device)
-    if (not out.is_contiguous() or out.dtype != torch.complex64
+    if (not out.is_contiguous() or out.dtype != torch.complex64 or _is_lazy(out)
             or tuple(out.shape) != (npol, M // alpha, ncols)):
         raise ValueError("out must be a contiguous complex64 [npol, M/alpha, ncols] tensor")
     _check(lib().mg_prune_columns(npol, M, ncols, int(alpha), int(support_z), ztaps.data_ptr(),
@@ -648,11 +673,14 @@ class Imager:
               y0: int = 0, out_ny: Optional[int] = None,
               out: Optional[torch.Tensor] = None) -> torch.Tensor:
         out_ny = self.ny if out_ny is None else int(out_ny)
+        grid = _stored(grid)
         if (grid.dtype != torch.complex64 or not grid.is_contiguous()
                 or tuple(grid.shape) != (self.npol, self.ny, self.nx)):
             raise ValueError(f"grid must be complex64 [{self.npol}, {self.ny}, {self.nx}]")
         if corr_x.numel() != self.nx or corr_y.numel() != out_ny:
             raise ValueError("corrector lengths must be nx and out_ny")
+        if out is not None and _is_lazy(out):
+            raise ValueError("out must not be a conjugate view")
         if out is None:
             out = torch.empty(self.npol, out_ny, self.nx, dtype=torch.complex64,
                               device=self.device)
@@ -741,10 +769,13 @@ class WStackImager:
               fov_x: float, fov_y: float, dw: float,
               out: Optional[torch.Tensor] = None) -> torch.Tensor:
         shape = (self.npol, self.layers, self.ny, self.nx)
+        grids = _stored(grids)
         if grids.dtype != torch.complex64 or not grids.is_contiguous() or tuple(grids.shape) != shape:
             raise ValueError(f"grids must be complex64 {list(shape)}")
         if corr_x.numel() != self.nx or corr_y.numel() != self.ny:
             raise ValueError("corrector lengths must be nx and ny")
+        if out is not None and _is_lazy(out):
+            raise ValueError("out must not be a conjugate view")
         if out is None:
             out = torch.empty(self.npol, self.ny, self.nx, dtype=torch.complex64,
                               device=self.device)
