@@ -1,0 +1,48 @@
+"""chi^2 over a plan that is not the library's plain one: a Plan subclass with
+its own gridding keeps the separate steps, so its gradient goes through that
+method."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2111_04141_amd import autograd as AG
+from paper_2111_04141_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+N, NREC, BETA, S = 64, 400, 4, 7
+
+
+def _inputs():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2111_04141_amd import api
+    rng = np.random.Generator(np.random.PCG64(8))
+    uvw = torch.from_numpy(rng.uniform(-N / 3, N / 3, (NREC, 3))).cuda()
+    bank = api.KernelBank("separable", torch.from_numpy(W.pswf_taps(S, BETA)).float().cuda(),
+                          support=S)
+
+    def cplx(*shape):
+        x = rng.standard_normal(shape) + 1j * rng.standard_normal(shape)
+        return torch.from_numpy(x.astype(np.complex64)).cuda()
+    return api, (api.GridSpec(N, N, 2, BETA, 1.0, 1.0), bank, uvw), cplx(2, N, N), cplx(NREC, 2)
+
+
+def test_subclass_gridding_is_used():
+    api, args, model, obs = _inputs()
+
+    class Masked(api.Plan):
+        """Grids onto the lower half of the grid only."""
+
+        def grid(self, vis, out=None):
+            g = super().grid(vis, out)
+            g[:, N // 2:] = 0
+            return g
+
+    m = model.clone().requires_grad_(True)
+    AG.chi2(m, Masked(*args), obs, 0.5).backward()
+    ref = model.clone().requires_grad_(True)
+    AG.chi2(ref, api.Plan(*args), obs, 0.5).backward()
+    top = float(ref.grad.abs().max())
+    assert float(m.grad[:, N // 2:].abs().max()) == 0.0
+    assert float((m.grad - ref.grad)[:, : N // 2].abs().max()) <= 1e-5 * top
