@@ -480,8 +480,9 @@ class Plan:
         """grid(factor vis) on a new grid, factor a float64 0-dim device tensor."""
         vis = _stored(vis)
         _check_vis(vis, self.nrec, self.spec.npol)
-        if not factor.is_cuda or factor.dtype != torch.float64 or factor.numel() != 1:
-            raise ValueError("factor must be a float64 device scalar")
+        if (not factor.is_cuda or factor.dtype != torch.float64 or factor.numel() != 1
+                or factor.device != self.device):
+            raise ValueError("factor must be a float64 scalar on the plan's device")
         out = torch.zeros(grid_shape(self.spec, self.bank), dtype=torch.complex64,
                           device=self.device)
         _check(lib().mg_plan_grid_scaled(self._h, vis.data_ptr(), factor.data_ptr(),

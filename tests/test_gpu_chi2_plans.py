@@ -1,6 +1,7 @@
-"""chi^2 over a plan that is not the library's plain one: a Plan subclass with
-its own gridding keeps the separate steps, so its gradient goes through that
-method."""
+"""chi^2 over plans and factors that are not the library's plain ones: a Plan
+subclass with its own gridding keeps the separate steps, so its gradient goes
+through that method, and a factor that lies on another device than the plan is
+refused before the library is called."""
 import numpy as np
 import pytest
 import torch
@@ -46,3 +47,20 @@ def test_subclass_gridding_is_used():
     top = float(ref.grad.abs().max())
     assert float(m.grad[:, N // 2:].abs().max()) == 0.0
     assert float((m.grad - ref.grad)[:, : N // 2].abs().max()) <= 1e-5 * top
+
+
+def test_factor_on_another_device_is_refused():
+    api, args, _, obs = _inputs()
+
+    class Elsewhere:
+        """A float64 scalar of a second GPU, as far as its checks can tell."""
+        is_cuda, dtype, device = True, torch.float64, torch.device("cuda", 1)
+
+        def numel(self):
+            return 1
+
+        def data_ptr(self):
+            raise AssertionError("read although it lies on another device")
+
+    with pytest.raises(ValueError):
+        api.Plan(*args).grid_scaled(obs, Elsewhere())
