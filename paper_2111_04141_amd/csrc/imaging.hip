@@ -4,8 +4,7 @@
 // sizes the centred unnormalised inverse transform
 //     I[y, x] = sum_k G[kv, ku] exp(+j2pi ((ku - nx/2)(x - nx/2)/nx + ...))
 // is (-1)^(x + y + nx/2 + ny/2) times the plain inverse FFT of
-// (-1)^(ku + kv) G, or, with the signs of G as a shift of its transform, times
-// the plain inverse FFT of G read at (x + nx/2 mod nx, y + ny/2 mod ny).
+// (-1)^(ku + kv) G.
 //  * Power-of-two sides (own_fft): two kernels of this file.  fft_rows_kernel
 //    transforms every row (its loads carry the signs), fft_columns_kernel
 //    every column and applies the signs, the correctors and the crop as it
@@ -13,9 +12,10 @@
 //    transform alone takes two row passes and two transpositions.  4 x 2048 x
 //    2048: rows 51 us (near a device copy's rate), columns 63 us, 124 us in all;
 //    with the library's transform between two kernels of its own 280 us.
-//  * Other even sides: the platform library's batched C2C transform, out of
-//    place, and one kernel for the shift, signs, correctors and crop (where the
-//    image is to take the scratch's place, the signs go in first instead).
+//  * Other even sides: the platform library's batched C2C transform, in place in
+//    the scratch, between a kernel that copies the grid with its signs and one
+//    for the other signs, correctors and crop.  (The library may overwrite its
+//    input even out of place, and the grid is read only.)
 // The Correction Step (Section 2.4.5, corrector h_co;
 // Section 2.4.4 for Hybrid Gridding, with the pruning kernel's corrector
 // along v) multiplies by separable corrector vectors, computed on the device
@@ -169,8 +169,7 @@ __global__ __launch_bounds__(fft_col_threads(LOGN)) void fft_columns_kernel(
     }
 }
 
-// work[p][y][x] = (-1)^(x + y) grid[p][y][x]: the signs of the input, where the
-// image takes the scratch's place and cannot be read shifted
+// work[p][y][x] = (-1)^(x + y) grid[p][y][x]
 __global__ __launch_bounds__(256) void shift_in_kernel(const float2 *__restrict__ grid,
                                                        float2 *__restrict__ work, int32_t nx,
                                                        int64_t total) {
@@ -187,15 +186,12 @@ __global__ __launch_bounds__(256) void shift_in_kernel(const float2 *__restrict_
     }
 }
 
-// image[p][y][x] = (-1)^(x + y0 + y + nx/2 + ny/2) corr_x[x] corr_y[y] times the
-// transform in work[p] at row y0 + y + ny/2 mod ny and column x + nx/2 mod nx
-// (shifted = 1: of the plain grid) or at row y0 + y and column x (0: of the
-// grid with its signs), y < out_ny.  (work and image may be the same buffer
-// where shifted = 0.)
+// image[p][y][x] = (-1)^(x + y0 + y + nx/2 + ny/2) corr_x[x] corr_y[y]
+//                  work[p][y0 + y][x], y < out_ny
+// (work and image may be the same buffer where nothing is cropped)
 __global__ __launch_bounds__(256) void correct_out_kernel(const float2 *work, float2 *image,
                                                           int32_t nx, int32_t ny, int32_t y0,
                                                           int32_t out_ny, int32_t npol,
-                                                          int32_t shifted,
                                                           const float *__restrict__ cx,
                                                           const float *__restrict__ cy) {
     const int64_t total = (int64_t)npol * out_ny * nx;
@@ -205,12 +201,7 @@ __global__ __launch_bounds__(256) void correct_out_kernel(const float2 *work, fl
         const int x = (int)(k - prow * nx);
         const int p = (int)(prow / out_ny);
         const int y = (int)(prow - (int64_t)p * out_ny);
-        int xs = x, ys = y0 + y;
-        if (shifted) {
-            xs = x < nx / 2 ? x + nx / 2 : x - nx / 2;
-            ys = ys < ny / 2 ? ys + ny / 2 : ys - ny / 2;
-        }
-        float2 v = work[((int64_t)p * ny + ys) * nx + xs];
+        float2 v = work[((int64_t)p * ny + y0 + y) * nx + x];
         float f = cx[x] * cy[y];
         if ((x + y0 + y + nx / 2 + ny / 2) & 1) f = -f;
         v.x *= f;
@@ -288,7 +279,7 @@ void wstack_columns_kernel(
     }
 }
 
-// Other sides: from the plain transforms of the layers.
+// Other sides: from the transforms of the layers.
 __global__ __launch_bounds__(256) void wstack_combine_kernel(
     const float2 *__restrict__ work, float2 *__restrict__ image, int32_t nx, int32_t ny,
     int32_t npol, int32_t layers, double dw, double fov_x, double fov_y,
@@ -302,10 +293,8 @@ __global__ __launch_bounds__(256) void wstack_combine_kernel(
         const int y = (int)(yx / nx);
         const int x = (int)(yx - (int64_t)y * nx);
         const double nm1 = w_n_minus_1(x, y, nx, ny, fov_x, fov_y);
-        const int xs = x < nx / 2 ? x + nx / 2 : x - nx / 2;
-        const int ys = y < ny / 2 ? y + ny / 2 : y - ny / 2;
         float2 sum = make_float2(0.0f, 0.0f);
-        const float2 *src = work + (int64_t)p * layers * plane + (int64_t)ys * nx + xs;
+        const float2 *src = work + (int64_t)p * layers * plane + yx;
         for (int j = 0; j < layers; ++j)
             add_screened(sum, src[(int64_t)j * plane],
                          ((double)j - 0.5 * (double)(layers - 1)) * dw, nm1);
@@ -375,10 +364,15 @@ mg_status library_plan(hipfftHandle *plan, int nx, int ny, int batch) {
     return MG_OK;
 }
 
-mg_status library_fft(hipfftHandle plan, const void *in, void *out, hipStream_t stream) {
+// The centred transforms (but for the signs of the output) of the nx x ny planes
+// of `grid`, `total` cells, in `work`.
+mg_status library_fft(hipfftHandle plan, const void *grid, void *work, int nx, int64_t total,
+                      hipStream_t stream) {
+    hipLaunchKernelGGL(shift_in_kernel, dim3(blocks_for(total)), dim3(256), 0, stream,
+                       (const float2 *)grid, (float2 *)work, nx, total);
     if (hipfftSetStream(plan, stream) != HIPFFT_SUCCESS) return set_error(MG_EDEVICE, "FFT stream");
-    const hipfftResult r = hipfftExecC2C(plan, (hipfftComplex *)const_cast<void *>(in),
-                                         (hipfftComplex *)out, HIPFFT_BACKWARD);
+    const hipfftResult r = hipfftExecC2C(plan, (hipfftComplex *)work, (hipfftComplex *)work,
+                                         HIPFFT_BACKWARD);
     if (r != HIPFFT_SUCCESS)
         return set_error(MG_EDEVICE, "FFT execution failed (" + std::to_string((int)r) + ")");
     return MG_OK;
@@ -441,17 +435,13 @@ mg_status mg_imager_exec(mg_imager *im, const void *grid, void *work, void *imag
                                corr_y);
         });
     } else {
-        const int32_t shifted = work != image;
-        const int64_t total = (int64_t)im->npol * im->ny * im->nx;
-        if (!shifted)
-            hipLaunchKernelGGL(shift_in_kernel, dim3(blocks_for(total)), dim3(256), 0, stream,
-                               (const float2 *)grid, (float2 *)work, im->nx, total);
-        const mg_status st = library_fft(im->plan, shifted ? grid : work, work, stream);
+        const mg_status st = library_fft(im->plan, grid, work, im->nx,
+                                         (int64_t)im->npol * im->ny * im->nx, stream);
         if (st != MG_OK) return st;
         hipLaunchKernelGGL(correct_out_kernel,
                            dim3(blocks_for((int64_t)im->npol * out_ny * im->nx)), dim3(256), 0,
                            stream, (const float2 *)work, (float2 *)image, im->nx, im->ny, y0,
-                           out_ny, im->npol, shifted, corr_x, corr_y);
+                           out_ny, im->npol, corr_x, corr_y);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(MG_EDEVICE, std::string("imaging kernels: ") + hipGetErrorString(e));
@@ -507,7 +497,9 @@ mg_status mg_wstack_imager_exec(mg_wstack_imager *im, const void *grids, void *w
                                fov_x, fov_y, corr_x, corr_y);
         });
     } else {
-        const mg_status st = library_fft(im->plan, grids, work, stream);
+        const mg_status st =
+            library_fft(im->plan, grids, work, im->nx,
+                        (int64_t)im->npol * im->layers * im->ny * im->nx, stream);
         if (st != MG_OK) return st;
         hipLaunchKernelGGL(wstack_combine_kernel,
                            dim3(blocks_for((int64_t)im->npol * im->ny * im->nx)), dim3(256), 0,
