@@ -144,8 +144,8 @@ __device__ inline void exchange_columns(float2 (&v)[16], float *s, int t, int c,
 // image[p][y][x] = (-1)^(x + y0 + y + nx/2 + ny/2) cx[x] cy[y] times the
 // transform of column x of work[p] at row y0 + y, y < out_ny.  (A workgroup has
 // read its columns before it stores them: work and image may be the same
-// buffer where nothing is cropped.)
-template <int LOGN>
+// buffer where nothing is cropped.)  PLAIN: the transform alone, uncropped.
+template <int LOGN, bool PLAIN>
 __global__ __launch_bounds__(fft_col_threads(LOGN)) void fft_columns_kernel(
     const float2 *work, float2 *image, int32_t nx, int32_t y0,
     int32_t out_ny, const float *__restrict__ cx, const float *__restrict__ cy) {
@@ -158,6 +158,11 @@ __global__ __launch_bounds__(fft_col_threads(LOGN)) void fft_columns_kernel(
 #pragma unroll
     for (int k = 0; k < 16; ++k) v[k] = src[(int64_t)k * T * nx];
     fft_inverse<LOGN>(v, t, [&](auto put) { exchange_columns<LOGN>(v, s_col, t, c, put); });
+    if constexpr (PLAIN) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) image[((int64_t)p * N + t + k * T) * nx + x] = v[k];
+        return;
+    }
     float f = cx[x];
     if ((x + t + nx / 2 + N / 2) & 1) f = -f;   // (T is even)
 #pragma unroll
@@ -279,7 +284,8 @@ void wstack_columns_kernel(
     }
 }
 
-// Other sides: from the transforms of the layers.
+// From the transforms of the layers: other sides, and power-of-two ones with too
+// few columns (wstack_fused).
 __global__ __launch_bounds__(256) void wstack_combine_kernel(
     const float2 *__restrict__ work, float2 *__restrict__ image, int32_t nx, int32_t ny,
     int32_t npol, int32_t layers, double dw, double fov_x, double fov_y,
@@ -302,6 +308,15 @@ __global__ __launch_bounds__(256) void wstack_combine_kernel(
         if ((x + y + nx / 2 + ny / 2) & 1) f = -f;
         image[k] = make_float2(sum.x * f, sum.y * f);
     }
+}
+
+// wstack_columns_kernel takes the layers of a column one after another, so its
+// columns alone have to fill the chip: four waves a SIMD, 1024 threads a CU.
+// Below that the layers' columns are transformed side by side, in place, and
+// combined in another pass.  One polarisation, 128 layers of 256^2: 563 us one
+// after another, 84 side by side; 16 of 2048^2 (which fill it): 503 and 595.
+bool wstack_fused(int64_t groups, int threads, int layers) {
+    return layers == 1 || groups * threads >= (int64_t)device_cus() * 1024;
 }
 
 int blocks_for(int64_t n) {
@@ -428,7 +443,7 @@ mg_status mg_imager_exec(mg_imager *im, const void *grid, void *work, void *imag
         fft_rows(log2_side(im->nx, 13), grid, work, (int64_t)im->npol * im->ny, stream);
         column_size(log2_side(im->ny, 12), [&](auto l) {
             constexpr int L = decltype(l)::value;
-            hipLaunchKernelGGL(fft_columns_kernel<L>,
+            hipLaunchKernelGGL((fft_columns_kernel<L, false>),
                                dim3((unsigned)(im->nx / fft_cols(L)), (unsigned)im->npol),
                                dim3(fft_col_threads(L)), fft_col_lds(L), stream,
                                (const float2 *)work, (float2 *)image, im->nx, y0, out_ny, corr_x,
@@ -485,27 +500,38 @@ mg_status mg_wstack_imager_exec(mg_wstack_imager *im, const void *grids, void *w
     if (!std::isfinite(fov_x) || !std::isfinite(fov_y) || !std::isfinite(dw))
         return set_error(MG_EINVAL, "fov and dw must be finite");
     if (work == image) return set_error(MG_EINVAL, "the image needs its own buffer");
-    if (own_fft(im->nx, im->ny)) {
+    const bool own = own_fft(im->nx, im->ny);
+    bool combine = !own;
+    if (own) {
         fft_rows(log2_side(im->nx, 13), grids, work, (int64_t)im->npol * im->layers * im->ny,
                  stream);
         column_size(log2_side(im->ny, 12), [&](auto l) {
             constexpr int L = decltype(l)::value;
-            hipLaunchKernelGGL(wstack_columns_kernel<L>,
-                               dim3((unsigned)(im->nx / fft_cols(L)), (unsigned)im->npol),
-                               dim3(fft_col_threads(L)), fft_col_lds(L), stream,
-                               (const float2 *)work, (float2 *)image, im->nx, im->layers, dw,
-                               fov_x, fov_y, corr_x, corr_y);
+            const unsigned tiles = (unsigned)(im->nx / fft_cols(L));
+            combine = !wstack_fused((int64_t)tiles * im->npol, fft_col_threads(L), im->layers);
+            if (combine)
+                hipLaunchKernelGGL((fft_columns_kernel<L, true>),
+                                   dim3(tiles, (unsigned)(im->npol * im->layers)),
+                                   dim3(fft_col_threads(L)), fft_col_lds(L), stream,
+                                   (const float2 *)work, (float2 *)work, im->nx, 0, im->ny,
+                                   nullptr, nullptr);
+            else
+                hipLaunchKernelGGL(wstack_columns_kernel<L>, dim3(tiles, (unsigned)im->npol),
+                                   dim3(fft_col_threads(L)), fft_col_lds(L), stream,
+                                   (const float2 *)work, (float2 *)image, im->nx, im->layers, dw,
+                                   fov_x, fov_y, corr_x, corr_y);
         });
     } else {
         const mg_status st =
             library_fft(im->plan, grids, work, im->nx,
                         (int64_t)im->npol * im->layers * im->ny * im->nx, stream);
         if (st != MG_OK) return st;
+    }
+    if (combine)
         hipLaunchKernelGGL(wstack_combine_kernel,
                            dim3(blocks_for((int64_t)im->npol * im->ny * im->nx)), dim3(256), 0,
                            stream, (const float2 *)work, (float2 *)image, im->nx, im->ny,
                            im->npol, im->layers, dw, fov_x, fov_y, corr_x, corr_y);
-    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(MG_EDEVICE, std::string("W-stacking kernels: ") + hipGetErrorString(e));
     return MG_OK;
