@@ -396,7 +396,8 @@ mg_status mg_wstack_imager_destroy(mg_wstack_imager *im);
  * central beta S_p + 1 samples per axis, row (v offset) major: the layout
  * the gridders take.  The bank is normalised so its largest |tap| is 1.  At
  * w = 0 a plane is the outer product of the (zero-padded) base taps.
- * Computed in FP64 (cosine transforms of one quadrant) and stored as out_dtype
+ * Computed in FP64 (cosine transforms of one quadrant; planes of beta*S above
+ * 1024 by the platform library's Z2Z FFT) and stored as out_dtype
  * (MG_F32: complex64; MG_F16 / MG_BF16: re, im pairs). */
 mg_status mg_wkernel_bank_size(int32_t nplanes, const int32_t *plane_support, int32_t beta,
                                int64_t *bank_elems, size_t *workspace_bytes);
@@ -407,9 +408,13 @@ mg_status mg_wkernel_bank_size(int32_t nplanes, const int32_t *plane_support, in
  * image quadrants, their transforms and tables), passed with its size, in use
  * until the queued work is done.  The work is queued on `stream` (no host
  * copies, no synchronisation); builds with workspaces of their own may
- * overlap.  Errors: MG_EINVAL (sizes out of range, beta*S
+ * overlap.  Planes of beta*S above 1024: the FFT plans (one per plane size and
+ * device, created on first use) are kept for the life of the process, their
+ * work area is allocated and released stream-ordered inside the call.
+ * Errors: MG_EINVAL (sizes out of range, beta*S
  * odd or above 4096, a plane narrower than the base kernel, fov not
- * positive, non-finite w, null pointers, workspace too small), MG_EDEVICE. */
+ * positive, non-finite w, null pointers, workspace too small), MG_ENOMEM,
+ * MG_EDEVICE. */
 mg_status mg_wkernel_bank(int32_t nplanes, const int32_t *plane_support, const double *plane_w,
                           int32_t beta, int32_t base_len, const double *base_taps, double fov,
                           mg_dtype out_dtype, void *bank, int64_t *plane_offset, void *workspace,

@@ -31,13 +31,20 @@
 //                  |K|
 //   store_kernel   bank = K / max, converted to the output tap format, row
 //                  (v offset) major.
+// The products grow with H^3 and a transform with H^2 log H: planes of H above
+// kCosineMax take the platform library's transform of the full M x M image, in
+// place, and quadrant_kernel keeps K and its maximum.
 // All steps in FP64.  Plane parameters travel as kernel arguments, so the
 // call copies nothing from the host and does not synchronise.
 #include <hip/hip_runtime.h>
+#include <hipfft/hipfft.h>
 
 #include <algorithm>
 #include <cmath>
+#include <map>
+#include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "internal.h"
@@ -48,7 +55,7 @@ namespace {
 // The planes of a bank (kernel argument).  The workspace of plane p, in
 // doubles from ws[p]: cos table [M], taper [H + 1], padded to even, then
 // complex X [H + 1][H + 1], B [H + 1][h + 1], K [h + 1][h + 1], H = M/2 = beta
-// S, h = H/2.
+// S, h = H/2; H above kCosineMax: X [M][M] (its transform takes its place), K.
 struct BankPlanes {
     int64_t ws[kMaxPlanes];
     int64_t bank[kMaxPlanes];   // complex elements into the bank
@@ -63,9 +70,14 @@ struct PlaneWork {
 };
 
 constexpr int kMaxBank = 512;   // largest beta S whose cos table goes to LDS
+// Largest beta S by cosine products: one plane of 1024 takes 151 us (190 by a
+// transform of its full image), one of 2048 1122 us (678), of 4096 11.4 ms
+// (3.2).
+constexpr int kCosineMax = 1024;
 
 constexpr int64_t table_doubles(int64_t H) { return (2 * H + H + 1 + 1) & ~int64_t(1); }
 constexpr int64_t work_doubles(int64_t H) {
+    if (H > kCosineMax) return table_doubles(H) + 2 * (4 * H * H + (H / 2 + 1) * (H / 2 + 1));
     return table_doubles(H) + 2 * ((H + 1) * (H + 1) + (H + 1) * (H / 2 + 1) + (H / 2 + 1) * (H / 2 + 1));
 }
 
@@ -77,6 +89,11 @@ __device__ inline PlaneWork plane_work(const BankPlanes &P, int p, int beta, dou
     w.ct = ws + P.ws[p];
     w.taper = w.ct + w.M;
     w.X = reinterpret_cast<double2 *>(w.ct + table_doubles(w.H));
+    if (w.H > kCosineMax) {
+        w.B = nullptr;
+        w.K = w.X + (int64_t)w.M * w.M;
+        return w;
+    }
     w.B = w.X + (int64_t)(w.H + 1) * (w.H + 1);
     w.K = w.B + (int64_t)(w.H + 1) * (w.h + 1);
     return w;
@@ -108,18 +125,25 @@ __global__ __launch_bounds__(256) void tables_kernel(BankPlanes P, int32_t beta,
 __global__ __launch_bounds__(256) void screen_kernel(BankPlanes P, int32_t beta, double fov,
                                                      double *__restrict__ ws) {
     const PlaneWork w = plane_work(P, blockIdx.y, beta, ws);
-    const int side = w.H + 1;
+    // the quadrant, weighted; or the whole image in transform order
+    const bool full = w.H > kCosineMax;
+    const int side = full ? w.M : w.H + 1;
     const double wp = P.w[blockIdx.y];
     for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < side * side;
          k += gridDim.x * blockDim.x) {
-        const int i = k / side, j = k - i * side;
+        int i = k / side, j = k - i * side;
+        if (full) {   // (even along both axes)
+            i = min(i, w.M - i);
+            j = min(j, w.M - j);
+        }
         const double l = (double)i * ((double)beta / (double)w.M) * fov;
         const double m = (double)j * ((double)beta / (double)w.M) * fov;
         const double r2 = l * l + m * m;
         const double nn = r2 < 1.0 ? sqrt(1.0 - r2) : 0.0;
         double sn, cs;
         sincospi(2.0 * (wp * (nn - 1.0)), &sn, &cs);
-        const double e = (i == 0 || i == w.H ? 1.0 : 2.0) * (j == 0 || j == w.H ? 1.0 : 2.0);
+        double e = 1.0;
+        if (!full) e = (i == 0 || i == w.H ? 1.0 : 2.0) * (j == 0 || j == w.H ? 1.0 : 2.0);
         const double a = e * w.taper[i] * w.taper[j];
         w.X[k] = make_double2(a * cs, a * sn);
     }
@@ -146,7 +170,7 @@ __global__ __launch_bounds__(256) void cosine_kernel(BankPlanes P, int32_t beta,
     const int rows = PASS == 0 ? w.H + 1 : w.h + 1, cols = w.h + 1;
     const int tc = (cols + 15) / 16, tiles = ((rows + 15) / 16) * tc;
     const int tile = blockIdx.x;
-    if (tile >= tiles) return;
+    if (tile >= tiles || w.H > kCosineMax) return;
     __shared__ double s_cos[2 * kMaxBank];
     __shared__ f64x4 s_part[2][3][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, kk = lane >> 4;
@@ -218,6 +242,24 @@ __global__ __launch_bounds__(256) void cosine_kernel(BankPlanes P, int32_t beta,
     }
 }
 
+// K of plane p from its transform, and the largest |K|.
+__global__ __launch_bounds__(256) void quadrant_kernel(BankPlanes P, int32_t p, int32_t beta,
+                                                       double *__restrict__ ws,
+                                                       unsigned long long *mx) {
+    const PlaneWork w = plane_work(P, p, beta, ws);
+    const int side = w.h + 1;
+    double best = 0.0;
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < side * side;
+         k += gridDim.x * blockDim.x) {
+        const int a = k / side, b = k - a * side;
+        const double2 v = w.X[(int64_t)a * w.M + b];
+        w.K[k] = v;
+        best = fmax(best, sqrt(v.x * v.x + v.y * v.y));
+    }
+    for (int o = 32; o > 0; o >>= 1) best = fmax(best, __shfl_xor(best, o));
+    if ((threadIdx.x & 63) == 0) atomicMax(mx, (unsigned long long)__double_as_longlong(best));
+}
+
 template <typename OutT> __device__ inline void store_tap(OutT *bank, int64_t i, double re, double im);
 template <> __device__ inline void store_tap<float>(float *bank, int64_t i, double re, double im) {
     bank[2 * i] = (float)re;
@@ -257,6 +299,7 @@ struct Layout {
     BankPlanes planes;
     int64_t bank_elems = 0;
     int64_t H_max = 0;          // largest beta S
+    int64_t H_cosine = 0;       // the same up to kCosineMax (0: none)
     size_t bytes = 0, off_max = 0;
 };
 
@@ -269,7 +312,7 @@ mg_status make_layout(int32_t nplanes, const int32_t *sup, int32_t beta, Layout 
         const int S = sup[p];
         if (S < 1 || S > kMaxSupport) return set_error(MG_EINVAL, "plane support must be in 1..64");
         if (((int64_t)beta * S) % 2) return set_error(MG_EINVAL, "beta * support must be even");
-        // the FP64 image quadrant of a plane is (beta S + 1)^2 x 16 bytes
+        // the FP64 image of a large plane is (2 beta S)^2 x 16 bytes
         if ((int64_t)beta * S > 4096) return set_error(MG_EINVAL, "beta * support must be <= 4096");
         const int64_t H = (int64_t)beta * S;
         L.planes.S[p] = (uint8_t)S;
@@ -278,10 +321,91 @@ mg_status make_layout(int32_t nplanes, const int32_t *sup, int32_t beta, Layout 
         L.bank_elems += (H + 1) * (H + 1);
         doubles += work_doubles(H);
         L.H_max = std::max(L.H_max, H);
+        if (H <= kCosineMax) L.H_cosine = std::max(L.H_cosine, H);
     }
     L.off_max = arena_round(sizeof(double) * (size_t)doubles);
     L.bytes = L.off_max + arena_round(sizeof(unsigned long long));
     return MG_OK;
+}
+
+// FFT plans by (device, M), kept for the life of the process, with the bytes of
+// work area one needs.  Builds bring a work area of their own each, so a plan's
+// transforms may overlap on several streams.
+struct BankFft {
+    hipfftHandle h = nullptr;
+    size_t work = 0;
+};
+std::mutex g_fft_mu;
+std::map<std::pair<int, int>, BankFft> g_fft;
+
+// (with g_fft_mu held)
+hipfftResult bank_fft(int dev, int M, BankFft *out) {
+    auto it = g_fft.find({dev, M});
+    if (it == g_fft.end()) {
+        BankFft f;
+        hipfftResult r = hipfftCreate(&f.h);
+        if (r != HIPFFT_SUCCESS) return r;
+        r = hipfftSetAutoAllocation(f.h, 0);
+        if (r == HIPFFT_SUCCESS) r = hipfftMakePlan2d(f.h, M, M, HIPFFT_Z2Z, &f.work);
+        if (r == HIPFFT_SUCCESS) r = hipfftGetSize(f.h, &f.work);
+        if (r != HIPFFT_SUCCESS) {
+            hipfftDestroy(f.h);
+            return r;
+        }
+        it = g_fft.emplace(std::make_pair(dev, M), f).first;
+    }
+    *out = it->second;
+    return HIPFFT_SUCCESS;
+}
+
+// Transforms and quadrants of the planes above kCosineMax.
+mg_status large_planes(const Layout &L, int32_t nplanes, int32_t beta, double *ws,
+                       unsigned long long *mx, hipStream_t stream) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return set_error(MG_EDEVICE, "no device");
+    auto fft_error = [](hipfftResult r) {
+        return set_error(MG_EDEVICE, "FFT failed (" + std::to_string((int)r) + ")");
+    };
+    // one work area for them all, in the stream's order
+    size_t bytes = 0;
+    for (int p = 0; p < nplanes; ++p) {
+        const int H = beta * (int)L.planes.S[p];
+        if (H <= kCosineMax) continue;
+        std::lock_guard<std::mutex> lk(g_fft_mu);
+        BankFft f;
+        const hipfftResult r = bank_fft(dev, 2 * H, &f);
+        if (r != HIPFFT_SUCCESS) return fft_error(r);
+        bytes = std::max(bytes, f.work);
+    }
+    void *area = nullptr;
+    if (bytes) {
+        const hipError_t e = scratch_alloc(&area, bytes, stream);
+        if (e != hipSuccess)
+            return set_error(MG_ENOMEM, std::string("FFT work area: ") + hipGetErrorString(e));
+    }
+    hipfftResult r = HIPFFT_SUCCESS;
+    for (int p = 0; p < nplanes && r == HIPFFT_SUCCESS; ++p) {
+        const int H = beta * (int)L.planes.S[p];
+        if (H <= kCosineMax) continue;
+        hipfftDoubleComplex *img =
+            reinterpret_cast<hipfftDoubleComplex *>(ws + L.planes.ws[p] + table_doubles(H));
+        {
+            // the plan is shared: its stream and work area are set and the
+            // transform queued under the lock
+            std::lock_guard<std::mutex> lk(g_fft_mu);
+            BankFft f;
+            r = bank_fft(dev, 2 * H, &f);
+            if (r == HIPFFT_SUCCESS) r = hipfftSetStream(f.h, stream);
+            if (r == HIPFFT_SUCCESS && f.work) r = hipfftSetWorkArea(f.h, area);
+            if (r == HIPFFT_SUCCESS) r = hipfftExecZ2Z(f.h, img, img, HIPFFT_FORWARD);
+        }
+        const int64_t n = (int64_t)(H / 2 + 1) * (H / 2 + 1);
+        if (r == HIPFFT_SUCCESS)
+            hipLaunchKernelGGL(quadrant_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)),
+                               dim3(256), 0, stream, L.planes, p, beta, ws, mx);
+    }
+    if (area) scratch_free(area, stream);
+    return r == HIPFFT_SUCCESS ? MG_OK : fft_error(r);
 }
 
 }  // namespace
@@ -327,19 +451,26 @@ mg_status mg_wkernel_bank(int32_t nplanes, const int32_t *plane_support, const d
         reinterpret_cast<unsigned long long *>(static_cast<char *>(workspace) + L.off_max);
     // grids for the largest plane; the others' spare workgroups have nothing
     // to do
-    const int64_t side = L.H_max + 1, tile_rows = (side + 15) / 16,
-                  tile_cols = (L.H_max / 2 + 1 + 15) / 16;
+    const int64_t side = L.H_max > kCosineMax ? 2 * L.H_max : L.H_max + 1;
+    const int64_t tile_rows = (L.H_cosine + 1 + 15) / 16,
+                  tile_cols = (L.H_cosine / 2 + 1 + 15) / 16;
     auto over = [&](int64_t groups) {
         return dim3((unsigned)std::max<int64_t>(1, groups), (unsigned)nplanes);
     };
     const dim3 elems = over(std::min<int64_t>((side * side + 255) / 256, 4096));
-    hipLaunchKernelGGL(tables_kernel, over((side + 3) / 4), dim3(256), 0, stream, L.planes, beta,
+    hipLaunchKernelGGL(tables_kernel, over((L.H_max + 1 + 3) / 4), dim3(256), 0, stream, L.planes, beta,
                        base_len, base_taps, ws, mx);
     hipLaunchKernelGGL(screen_kernel, elems, dim3(256), 0, stream, L.planes, beta, fov, ws);
-    hipLaunchKernelGGL(cosine_kernel<0>, over(tile_rows * tile_cols), dim3(256), 0,
-                       stream, L.planes, beta, ws, mx);
-    hipLaunchKernelGGL(cosine_kernel<1>, over(tile_cols * tile_cols), dim3(256), 0,
-                       stream, L.planes, beta, ws, mx);
+    if (L.H_cosine) {
+        hipLaunchKernelGGL(cosine_kernel<0>, over(tile_rows * tile_cols), dim3(256), 0,
+                           stream, L.planes, beta, ws, mx);
+        hipLaunchKernelGGL(cosine_kernel<1>, over(tile_cols * tile_cols), dim3(256), 0,
+                           stream, L.planes, beta, ws, mx);
+    }
+    if (L.H_max > kCosineMax) {
+        st = large_planes(L, nplanes, beta, ws, mx, stream);
+        if (st != MG_OK) return st;
+    }
     const unsigned long long *cmx = mx;
     if (out_dtype == MG_F16)
         hipLaunchKernelGGL(store_kernel<__half>, elems, dim3(256), 0, stream, L.planes, beta, ws,
