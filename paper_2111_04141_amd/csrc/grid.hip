@@ -172,11 +172,17 @@ __device__ inline uint32_t next_unit(uint32_t *queue, uint32_t *slot) {
 // against scalar-unit visibilities, v_fma_f32 and global taps: S <= 8 3.29 ->
 // 2.70 ms, S <= 16 7.01 -> 6.80 ms, S <= 32 6.53 -> 6.22 ms; separable 7 x 7,
 // 10.08M records on 2048^2: 0.714 -> 0.426 ms.
-// Waves per workgroup: eight (two such workgroups share a CU's LDS for
+// Supports 9 to 16 with their taps in global memory keep the vector units: their
+// records are read on the scalar unit, in batches, by v_fma_f32 (the same bits),
+// and where no chunk of the call can have its table in LDS four waves share a
+// region, so that more regions fit a CU and a short chunk is cut into fewer
+// parts.  Records spread evenly over 1024^2, matrix cores and eight waves in
+// both: S = 16, W-projection, beta 8, 100,000 records of one polarisation 129 ->
+// 91 us; 4M records: S = 12 909 -> 822, separable beta 64 715 -> 605.
+// Waves per workgroup (NW): eight (two such workgroups share a CU's LDS for
 // supports up to 32, and the instances with several slots per lane are held
 // to four waves per SIMD: beyond 128 VGPRs the eight-slot instance ran a
-// third slower at three waves per SIMD).
-constexpr int kWindowWaves = 8;
+// third slower at three waves per SIMD), or those four.
 // Largest support of each window instance and its LDS region: 8 planes
 // (polarisations x re/im) of int32, each plane kWindowTile + S - 1 cells
 // square at most.  The plane stride is a compile-time constant, so the eight
@@ -199,6 +205,13 @@ constexpr size_t kWindowLds = 80 * 1024;
 // A group of one plane copies its table once per workgroup whatever the chunk:
 // 100,800 records on 1024^2, in chunks of 64: 67 us in place of 71.
 constexpr uint32_t kStagePerPhase = 8;
+// ... and in all: with chunks of 64 records (calls of less than half a million)
+// four waves on global taps are the faster (100,000 records, W-projection, beta
+// 2, S = 16, one polarisation: 128 -> 91 us).
+constexpr uint32_t kStageLeast = 128;
+__host__ __device__ constexpr uint32_t stage_records(uint32_t beta) {
+    return kStagePerPhase * beta * beta > kStageLeast ? kStagePerPhase * beta * beta : kStageLeast;
+}
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -208,15 +221,33 @@ __device__ inline f32x4 mfma_col(float a, float b, f32x4 acc) {
     return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, acc, 4, BLOCK, 0);
 }
 
-template <int KMAX, int TEAM, bool SEP, typename TapT>
-__global__ __launch_bounds__(kWave * kWindowWaves)
+// the four complex sums of a slot += w times a record's visibilities
+template <bool SEP>
+__device__ inline void fma_record(f32x4 &a0, f32x4 &a1, const float2 w, const RecVis &f) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        f32x4 &a = q < 2 ? a0 : a1;
+        const int e = 2 * (q & 1);
+        if constexpr (SEP) {
+            a[e] = fmaf(w.x, f.vr[q], a[e]);
+            a[e + 1] = fmaf(w.x, f.vi[q], a[e + 1]);
+        } else {
+            a[e] = fmaf(w.x, f.vr[q], fmaf(w.y, -f.vi[q], a[e]));
+            a[e + 1] = fmaf(w.x, f.vi[q], fmaf(w.y, f.vr[q], a[e + 1]));
+        }
+    }
+}
+
+template <int KMAX, int TEAM, int NW, bool SEP, typename TapT>
+__global__ __launch_bounds__(kWave * NW)
 __attribute__((amdgpu_waves_per_eu(4))) void grid_window_kernel(
     const RecMeta *__restrict__ smeta, const float *__restrict__ svis, float *__restrict__ grid,
     const TapT *__restrict__ taps, const Chunk *__restrict__ chunks,
     const uint32_t *__restrict__ bucket_cfirst, const uint2 *__restrict__ units,
     const uint32_t *__restrict__ group_nunits, const PlaneLayout *__restrict__ planes,
     const int32_t *__restrict__ uinfo, uint32_t *__restrict__ queue, GridParams prm) {
-    constexpr int NW = kWindowWaves;
+    // (the eight-slot class has no room for a table beside its region)
+    constexpr bool TABLE = KMAX < 8 && NW == 8;
     constexpr int NTEAMS = NW / TEAM;
     constexpr int PS = window_plane(KMAX);   // plane stride (cells)
     // [8][PS], plane q holding [RH][RW], then the workgroup's unit slot (the
@@ -322,7 +353,8 @@ __attribute__((amdgpu_waves_per_eu(4))) void grid_window_kernel(
             const uint32_t tap_off = planes[pc].tap_off;
             const uint32_t ntap = beta * beta * (uint32_t)(S * S);   // phase-major S x S blocks
             bool in_lds = staged == pc;
-            if (!in_lds && ch.len >= kStagePerPhase * beta * beta && ntap * kElemLds <= prm.tab_bytes) {
+            if (TABLE && !in_lds && ch.len >= stage_records(beta) &&
+                ntap * kElemLds <= prm.tab_bytes) {
                 __syncthreads();   // the previous table's readers are done
                 stage_taps<SEP, TapT>(s_tab, taps, tap_off, (uint32_t)S, beta, NW * kWave);
                 __syncthreads();
@@ -474,7 +506,66 @@ __attribute__((amdgpu_waves_per_eu(4))) void grid_window_kernel(
                 const uint32_t len = ch.len;
                 const uint32_t rb = ch.start + (uint32_t)(((uint64_t)len * team) / NTEAMS);
                 const uint32_t re = ch.start + (uint32_t)(((uint64_t)len * (team + 1)) / NTEAMS);
-                if (rb < re) {
+                if constexpr (KMAX == 4 && !LDS) {
+                    // records on the scalar unit, in batches: the next batch's
+                    // loads are issued after the current batch has been consumed
+                    // (scalar loads complete out of order: waiting for one is
+                    // waiting for all), so they overlap its multiply-adds
+                    if (rb < re) {
+                        RecMeta nm[kBatch];
+                        float4 na4[kBatch], nb4[kBatch];
+                        // the record arrays are padded (kRecPad entries), so a
+                        // batch may run past the chunk's end (not used)
+                        const RecMeta *pm = smeta + rb;
+                        const float4 *pv = reinterpret_cast<const float4 *>(svis) + 2 * (size_t)rb;
+                        auto load_batch = [&]() {
+#pragma unroll
+                            for (int i = 0; i < kBatch; ++i) {
+                                nm[i] = pm[i];
+                                na4[i] = pv[2 * i];
+                                nb4[i] = pv[2 * i + 1];
+                            }
+                            pm += kBatch;
+                            pv += 2 * kBatch;
+                        };
+                        uint32_t last_kuv = kNoCell;
+                        load_batch();
+                        wait_scalar_loads();
+                        for (uint32_t r = rb; r < re; r += kBatch) {
+                            RecMeta mm[kBatch];
+                            float4 va4[kBatch], vb4[kBatch];
+#pragma unroll
+                            for (int i = 0; i < kBatch; ++i) {
+                                mm[i] = nm[i];
+                                va4[i] = na4[i];
+                                vb4[i] = nb4[i];
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                            load_batch();
+#pragma unroll
+                            for (int i = 0; i < kBatch; ++i) {
+                                if (r + (uint32_t)i < re) {
+                                    if (mm[i].kuv != last_kuv) {
+                                        last_kuv = mm[i].kuv;
+                                        window_update(last_kuv);
+                                    }
+                                    const RecVis f = unpack_vis(va4[i], vb4[i]);
+                                    uint32_t tv;
+                                    const uint32_t t = tap_term(mm[i], &tv);
+                                    float2 w[KD];
+                                    issue(t, tv, w);
+#pragma unroll
+                                    for (int k = 0; k < KD; ++k)
+                                        fma_record<SEP>(acc0[k], acc1[k], w[k], f);
+                                }
+                            }
+                        }
+#pragma unroll
+                        for (int k = 0; k < KD; ++k)
+                            if (((valid_bits >> k) & 1u) && cell[k] != kNoCell)
+                                commit(acc0[k], acc1[k], cell[k]);
+                    }
+                } else if (rb < re) {
                     // eight records at a time: lane 8 i + c of `a` holds
                     // component c of record i; lanes past the range repeat its
                     // end.  Records go in pairs: the pair's columns are in
@@ -610,8 +701,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void grid_window_kernel(
                     }
                 }
             };
-            // (the eight-slot class has no room for a table beside its region)
-            if constexpr (KMAX == 8)
+            if constexpr (!TABLE)
                 run_kd(std::false_type{});
             else if (in_lds)
                 run_kd(std::true_type{});
@@ -1062,11 +1152,12 @@ struct GridPtrs {
 };
 
 // `table`: bytes of the largest tap table of the launch's planes that fits
-// beside the region with two workgroups to a CU (0: none).
-template <int KMAX, int TEAM, bool SEP, typename TapT>
+// beside the region with two workgroups to a CU and that a chunk of the call can
+// be long enough for (0: none).
+template <int KMAX, int TEAM, int NW, bool SEP, typename TapT>
 void launch_window(const GridPtrs &a, GridParams prm, size_t table, hipStream_t stream) {
-    auto kern = grid_window_kernel<KMAX, TEAM, SEP, TapT>;
-    const int threads = kWave * kWindowWaves;
+    auto kern = grid_window_kernel<KMAX, TEAM, NW, SEP, TapT>;
+    const int threads = kWave * NW;
     prm.tab_bytes = (uint32_t)table;
     const size_t lds = window_lds(KMAX) + table;
     hipLaunchKernelGGL(kern, dim3(resident_groups((const void *)kern, threads, lds)),
@@ -1092,14 +1183,16 @@ inline int region_blocks(int T, int S) {
 
 template <bool SEP, typename TapT>
 hipError_t launch_class(int cls, const GridPtrs &a, const GridParams &prm, int smax, int tile,
-                        const PlaneLayout *planes, hipStream_t stream) {
-    // largest tap table, in bytes, that fits the LDS left by the region
+                        const PlaneLayout *planes, uint32_t R, hipStream_t stream) {
+    // largest tap table, in bytes, that fits the LDS left by the region, if chunks
+    // of R records may have it there
     auto table = [&](size_t region) {
         size_t most = 0;
         for (int p = prm.p_lo; p < prm.p_hi; ++p) {
             const size_t w = (size_t)prm.beta * planes[p].S;
             const size_t t = w * w * (SEP ? sizeof(float) : 2 * sizeof(TapT));
-            if (region + t <= kWindowLds) most = std::max(most, t);
+            if (region + t <= kWindowLds && R >= stage_records((uint32_t)prm.beta))
+                most = std::max(most, t);
         }
         return (most + 7) & ~size_t(7);
     };
@@ -1108,9 +1201,16 @@ hipError_t launch_class(int cls, const GridPtrs &a, const GridParams &prm, int s
     if (cls <= 2 && (tile != kWindowTile || smax > window_smax(cls == 0 ? 1 : cls == 1 ? 4 : 8)))
         return hipErrorInvalidValue;
     switch (cls) {
-    case 0: launch_window<1, 1, SEP, TapT>(a, prm, table(window_lds(1)), stream); break;
-    case 1: launch_window<4, 1, SEP, TapT>(a, prm, table(window_lds(4)), stream); break;
-    case 2: launch_window<8, 2, SEP, TapT>(a, prm, 0, stream); break;
+    case 0: launch_window<1, 1, 8, SEP, TapT>(a, prm, table(window_lds(1)), stream); break;
+    case 1: {
+        const size_t t = table(window_lds(4));
+        if (t == 0)
+            launch_window<4, 1, 4, SEP, TapT>(a, prm, 0, stream);
+        else
+            launch_window<4, 1, 8, SEP, TapT>(a, prm, t, stream);
+        break;
+    }
+    case 2: launch_window<8, 2, 8, SEP, TapT>(a, prm, 0, stream); break;
     default:
         if (region_blocks(tile, smax) > 7 * 16) return hipErrorInvalidValue;
         launch_block<7, 16, SEP, TapT>(a, prm, stream);
@@ -1121,11 +1221,12 @@ hipError_t launch_class(int cls, const GridPtrs &a, const GridParams &prm, int s
 
 template <bool SEP>
 hipError_t launch_class_t(mg_dtype dt, int cls, const GridPtrs &a, const GridParams &prm,
-                          int smax, int tile, const PlaneLayout *planes, hipStream_t stream) {
+                          int smax, int tile, const PlaneLayout *planes, uint32_t R,
+                          hipStream_t stream) {
     switch (dt) {
-    case MG_F16: return launch_class<SEP, __half>(cls, a, prm, smax, tile, planes, stream);
-    case MG_BF16: return launch_class<SEP, __hip_bfloat16>(cls, a, prm, smax, tile, planes, stream);
-    default: return launch_class<SEP, float>(cls, a, prm, smax, tile, planes, stream);
+    case MG_F16: return launch_class<SEP, __half>(cls, a, prm, smax, tile, planes, R, stream);
+    case MG_BF16: return launch_class<SEP, __hip_bfloat16>(cls, a, prm, smax, tile, planes, R, stream);
+    default: return launch_class<SEP, float>(cls, a, prm, smax, tile, planes, R, stream);
     }
 }
 
@@ -1197,9 +1298,9 @@ mg_status launch_grid(const PlanState &P, const void *vis, void *grid, void *scr
         const int cls = P.planes[p0].cls;
         a.queue = gs.queues + p0;
         e = sep ? launch_class_t<true>(P.tap_dtype, cls, a, prm, smax, P.planes[p0].T,
-                                       P.planes.data(), stream)
+                                       P.planes.data(), (uint32_t)P.R, stream)
                 : launch_class_t<false>(P.tap_dtype, cls, a, prm, smax, P.planes[p0].T,
-                                        P.planes.data(), stream);
+                                        P.planes.data(), (uint32_t)P.R, stream);
         p0 = p1;
     }
     if (e == hipSuccess) e = hipGetLastError();
