@@ -182,6 +182,10 @@ __global__ __launch_bounds__(256) void index_taps_kernel(
 constexpr int kScanThreads = 1024;
 constexpr int kScanItems = 4;
 constexpr int kScanBlock = kScanThreads * kScanItems;
+// Blocks whose sums every workgroup adds up for itself; more are scanned in a
+// launch of their own.  Builds of 1000 records, added up and scanned: 4.2M
+// buckets (1024 blocks) 103 us both, 67M 646 and 555 us, 1074M 26.1 and 8.3 ms.
+constexpr int64_t kScanSums = 1024;
 
 __device__ inline uint2 add2(uint2 a, uint2 b) { return make_uint2(a.x + b.x, a.y + b.y); }
 
@@ -232,23 +236,50 @@ __global__ __launch_bounds__(kScanThreads) void scan_reduce_kernel(
     if (threadIdx.x == 0) block_sums[blockIdx.x] = total;
 }
 
+// Exclusive scan of the block sums, in place, by one workgroup.
+__global__ __launch_bounds__(kScanThreads) void scan_sums_kernel(uint2 *__restrict__ sums,
+                                                                 int64_t n) {
+    uint2 carry = make_uint2(0u, 0u);
+    for (int64_t first = 0; first < n; first += kScanBlock) {
+        const int64_t i = first + (int64_t)threadIdx.x * kScanItems;
+        uint2 v[kScanItems], mine = make_uint2(0u, 0u), total;
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            v[k] = i + k < n ? sums[i + k] : make_uint2(0u, 0u);
+            mine = add2(mine, v[k]);
+        }
+        uint2 run = add2(carry, block_exclusive_scan(mine, &total));
+#pragma unroll
+        for (int k = 0; k < kScanItems; ++k) {
+            if (i + k < n) sums[i + k] = run;
+            run = add2(run, v[k]);
+        }
+        carry = add2(carry, total);
+    }
+}
+
 // Writes cursor[i] (first record of bucket i, advanced by the scatter),
 // cstart[i] (first chunk of bucket i) and the chunks: bucket b with c records
-// -> ceil(c/R) chunks.  Every workgroup adds up the sums of the blocks before
-// its own (at most a few thousand words from L2).  Also plane_cfirst[p] = first
+// -> ceil(c/R) chunks.  The sum of the blocks before a workgroup's own is
+// block_sums[its number] where they have been scanned; else it adds them up.  Also plane_cfirst[p] = first
 // chunk of plane p's group, plane_cfirst[P] = cstart[n] = counters[2] = chunk
 // count, counters[1] = valid records (counters[3] counts the skipped records
 // placed by the scatter).
 __global__ __launch_bounds__(kScanThreads) void scan_chunks_kernel(
     const uint32_t *__restrict__ hist, int64_t n, uint32_t R,
-    const uint2 *__restrict__ block_sums, uint32_t *__restrict__ cursor,
+    const uint2 *__restrict__ block_sums, int32_t scanned, uint32_t *__restrict__ cursor,
     uint32_t *__restrict__ cstart, Chunk *__restrict__ chunks,
     const PlaneLayout *__restrict__ planes, int32_t nplanes, uint32_t *__restrict__ plane_cfirst,
     int64_t *__restrict__ counters) {
-    uint2 mine = make_uint2(0u, 0u), offset;
-    for (int j = threadIdx.x; j < (int)blockIdx.x; j += kScanThreads)
-        mine = add2(mine, block_sums[j]);
-    block_exclusive_scan(mine, &offset);
+    uint2 offset;
+    if (scanned) {
+        offset = block_sums[blockIdx.x];
+    } else {
+        uint2 mine = make_uint2(0u, 0u);
+        for (int j = threadIdx.x; j < (int)blockIdx.x; j += kScanThreads)
+            mine = add2(mine, block_sums[j]);
+        block_exclusive_scan(mine, &offset);
+    }
     const int64_t first = (int64_t)blockIdx.x * kScanBlock;
     const int64_t i = first + (int64_t)threadIdx.x * kScanItems;
     const uint4 c4 = counts_of(hist, i, n);
@@ -717,7 +748,8 @@ void launch_scatter(const PlanState &P, const void *uvw, int blocks, hipStream_t
 }
 }  // namespace
 
-// A build is seven launches (six where one block scans the buckets): the
+// A build is seven launches (six where one block scans the buckets, eight where
+// the block sums are scanned, one more for more than kPlaneArgs planes): the
 // smallest calls are bound by the launches, about 6 us each.
 mg_status plan_build(PlanState &P, const void *taps, const void *uvw, mg_dtype uvw_dtype,
                      hipStream_t stream) {
@@ -757,11 +789,14 @@ mg_status plan_build(PlanState &P, const void *taps, const void *uvw, mg_dtype u
         launch_index_t<float, false>(P, taps, uvw, tap_blocks, tap_per_plane, blocks, stream);
     else
         launch_index_t<double, false>(P, taps, uvw, tap_blocks, tap_per_plane, blocks, stream);
+    const bool scanned = nscan > kScanSums;
     if (nscan > 1)
         hipLaunchKernelGGL(scan_reduce_kernel, dim3((unsigned)nscan), dim3(kScanThreads), 0,
                            stream, P.hist, nb, R, P.sums);
+    if (scanned)
+        hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(kScanThreads), 0, stream, P.sums, nscan);
     hipLaunchKernelGGL(scan_chunks_kernel, dim3((unsigned)nscan), dim3(kScanThreads), 0, stream,
-                       P.hist, nb, R, P.sums, P.cursor, P.bucket_cfirst, P.chunks, P.d_planes, np,
+                       P.hist, nb, R, P.sums, (int32_t)scanned, P.cursor, P.bucket_cfirst, P.chunks, P.d_planes, np,
                        P.plane_cfirst, P.counters);
     if (nrec > 0) {
         if (lds && f32) launch_scatter<float, true>(P, uvw, blocks, stream);

@@ -60,3 +60,22 @@ def test_bank_of_a_large_plane(api, beta, support):
     print(f"[time] bank plane of beta S = {beta * support}: {ours:.0f} us, library transform "
           f"{lib:.0f} us", flush=True)
     assert ours < 1.6 * lib
+
+
+def test_plan_build_grows_with_the_buckets(api):
+    """Four times the buckets (268M -> 1074M) take about four times as long, and
+    not the eight times of a scan whose workgroups each add up all the blocks
+    before their own."""
+    import torch
+    beta, s, planes = 2, 8, 64
+    taps = torch.view_as_complex(torch.rand((beta * s + 1) ** 2, 2, device="cuda"))
+    bank = api.KernelBank("wproj", taps, plane_support=[s] * planes, plane_offset=[0] * planes,
+                          inv_dw=1.0)
+    uvw = torch.rand(1000, 3, device="cuda") - 0.5
+    us = []
+    for side in (32768, 65535):
+        spec = api.GridSpec(side, side, 1, beta, 30000.0, 30000.0)
+        us.append(_least_us(lambda: api.Plan(spec, bank, uvw).close(), 4))
+    torch.cuda.empty_cache()
+    print(f"[time] plan of 268M buckets {us[0]:.0f} us, of 1074M {us[1]:.0f} us", flush=True)
+    assert us[1] < 6.0 * us[0]
