@@ -95,6 +95,7 @@ __device__ inline void tap_layout(PlaneLayout *planes, int p, int block, int blo
 constexpr int64_t kLdsBuckets = 8192;
 constexpr int kLdsPerThread = 4;
 constexpr int kLdsRecords = 256 * kLdsPerThread;
+constexpr int64_t kLdsCallRecords = 1024 * (int64_t)kLdsRecords;
 
 // The plane layouts a plan is built with (kernel argument: up to kPlaneArgs a
 // launch, below the argument limit), and the words that start at zero.
@@ -393,7 +394,7 @@ __global__ __launch_bounds__(256) void scatter_kernel(DevGeom g,
 // and commit the tile's region once per unit rather than once per chunk.  units[first chunk of the group + k] = (first chunk, chunk count)
 // of the group's unit k; group_nunits[g] = unit count (cleared beforehand).
 // A wave's units are consecutive and in tile order.
-// One launch covers every group (blockIdx.y) and every tile (a thread each).
+// A launch covers its groups (blockIdx.y) and every tile (a thread each).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void unit_list_kernel(const PlaneLayout *__restrict__ planes,
                                                         GroupList groups,
@@ -749,8 +750,9 @@ void launch_scatter(const PlanState &P, const void *uvw, int blocks, hipStream_t
 }  // namespace
 
 // A build is seven launches (six where one block scans the buckets, eight where
-// the block sums are scanned, one more for more than kPlaneArgs planes): the
-// smallest calls are bound by the launches, about 6 us each.
+// the block sums are scanned, one more for more than kPlaneArgs planes, and the
+// unit lists of supports above 32): the smallest calls are bound by the launches,
+// about 6 us each.
 mg_status plan_build(PlanState &P, const void *taps, const void *uvw, mg_dtype uvw_dtype,
                      hipStream_t stream) {
     const int64_t nrec = P.nrec;
@@ -777,7 +779,7 @@ mg_status plan_build(PlanState &P, const void *taps, const void *uvw, mg_dtype u
     }
     const int tap_per_plane = (int)std::min<int64_t>(grid_blocks(most, 256), 1024);
     const int tap_blocks = tap_per_plane * np;
-    const bool lds = nb <= kLdsBuckets && nrec <= 1024 * (int64_t)kLdsRecords;
+    const bool lds = nb <= kLdsBuckets && nrec <= kLdsCallRecords;
     const int blocks = lds ? (int)std::max<int64_t>(1, (nrec + kLdsRecords - 1) / kLdsRecords)
                            : grid_blocks(nrec, 256);
     const bool f32 = uvw_dtype == MG_F32;
@@ -822,9 +824,34 @@ mg_status plan_build(PlanState &P, const void *taps, const void *uvw, mg_dtype u
     // tile once, so the launch has to cover them all, up to 65536 workgroups)
     int64_t tiles = 1;
     for (const PlaneLayout &L : P.planes) tiles = std::max(tiles, (int64_t)L.ntu * L.ntv);
-    hipLaunchKernelGGL(unit_list_kernel, dim3((unsigned)((tiles + 255) / 256), ngroups), dim3(256),
-                       0, stream, P.d_planes, groups, P.bucket_cfirst, P.chunks, R, P.units,
-                       P.group_nunits);
+    auto unit_lists = [&](const GroupList &list, int n) {
+        if (n > 0)
+            hipLaunchKernelGGL(unit_list_kernel, dim3((unsigned)((tiles + 255) / 256), n),
+                               dim3(256), 0, stream, P.d_planes, list, P.bucket_cfirst, P.chunks, R,
+                               P.units, P.group_nunits);
+    };
+    // Waves reserve their units as they come, which is nearly tile order where a
+    // group has the launch to itself, and the last tiles, at the edge of the grid,
+    // have the smallest units.  The blocked kernels of the largest supports have few
+    // and long units and wait for the last one: their groups get a launch each,
+    // except in calls small enough to be bound by launches.  W-projection benchmark
+    // workload, S > 32: degridding 1.94 ms, between 1.97 and 2.35 with the groups
+    // in one launch; gridding 1.39, 1.43 to 1.53.
+    if (nrec > kLdsCallRecords) {
+        GroupList rest{};
+        int n = 0;
+        for (int i = 0; i < ngroups; ++i) {
+            GroupList own{};
+            own.first[0] = groups.first[i];
+            if (P.planes[groups.first[i]].cls == 3)
+                unit_lists(own, 1);
+            else
+                rest.first[n++] = groups.first[i];
+        }
+        unit_lists(rest, n);
+    } else {
+        unit_lists(groups, ngroups);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(MG_EDEVICE, std::string("plan kernels: ") + hipGetErrorString(e));
     return MG_OK;
