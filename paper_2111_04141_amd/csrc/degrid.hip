@@ -356,9 +356,9 @@ __global__ __launch_bounds__(NW * kWave) void degrid_block_kernel(
 // tap, 18 cycles for 64 taps shared by four SIMDs against 54 cycles of
 // multiply-adds, and reduces every pair of records across the wave; it is kept
 // for chunks too short to pay for the table, and tables that do not fit.
-// Against the lane-per-tap path for all: W-projection benchmark workload (133.7M
-// records, 8192^2) S <= 8 3.87 -> 2.88 ms, S <= 16 9.88 -> 8.06 ms (runs of 8 and
-// 5 records a cell); separable 7 x 7, 10.08M records, 2048^2: 0.944 -> 0.522 ms.
+// Against the lane-per-tap path for all: 133.7M records of a W-projection bank,
+// 8192^2, S <= 8 3.80 -> 2.84 ms, S <= 16 9.69 -> 7.74 ms (runs of 8 and 5 records
+// a cell); separable 7 x 7, 10.08M records, 2048^2: 0.944 -> 0.522 ms.
 // Sixteen waves to a workgroup: 9.3 ms for S <= 16.
 //
 // Lane-per-tap path: the lanes of a wave take the taps of one record (tap
@@ -375,7 +375,8 @@ constexpr size_t cells_region(int ntap) {
 // LDS a workgroup's region and table may take so that two share a CU's 160 KB
 constexpr size_t kCellLds = 80 * 1024 - 256;
 // Records per oversampling phase a chunk needs for its plane's table to be
-// copied to LDS (as the window gridders': the copy reads the table once).
+// copied to LDS (as the window gridders': the copy reads the table once; their
+// figure, 8, is within 1 % on every timing case).
 constexpr uint32_t kCellStagePerPhase = 16;
 // Records per cell of its bounding box a chunk needs to be taken by cell: a
 // group of one record costs half as much again as on the lane-per-tap path.
@@ -743,17 +744,20 @@ constexpr int row_stride() { return 4 * PITCH + 8; }
 
 // Waves per workgroup of the taps kernel: eight share each staged region, whose
 // LDS limits how many workgroups a CU holds.
-constexpr int taps_waves(int) { return 8; }
+constexpr int kTapWaves = 8;
+// Records per reduction group: two, as a lane holds several taps (registers; the
+// reduction costs about the same per record either way).
+constexpr int kTapRecords = 2;
 
 template <int NTAP, int PITCH, int B, bool SEP, typename TapT>
-__global__ __launch_bounds__(kWave * taps_waves(NTAP)) void degrid_taps_kernel(
+__global__ __launch_bounds__(kWave * kTapWaves) void degrid_taps_kernel(
     const RecMeta *__restrict__ smeta, const uint32_t *__restrict__ sperm,
     const float *__restrict__ grid, float *__restrict__ vis_out, const TapT *__restrict__ taps,
     const Chunk *__restrict__ chunks, const uint32_t *__restrict__ bucket_cfirst,
     const uint2 *__restrict__ units, const uint32_t *__restrict__ group_nunits,
     const PlaneLayout *__restrict__ planes, uint32_t *__restrict__ queue, DegridParams prm) {
     constexpr int NV = B * 8;
-    constexpr int kWaves = taps_waves(NTAP);
+    constexpr int kWaves = kTapWaves;
     constexpr int kThreads = kWave * kWaves;
     constexpr uint32_t kElem = SEP ? sizeof(TapT) : 2 * sizeof(TapT);
     constexpr int kPitch = PITCH;
@@ -1037,10 +1041,8 @@ hipError_t launch_dt(const DegridPtrs &a, const DegridParams &prm, int tile, int
     // the region must fit the compile-time pitch and the taps the lanes
     if (tile + smax - 1 > PITCH || smax * smax > NTAP * 64) return hipErrorInvalidValue;
     const size_t lds = sizeof(float2) * (size_t)row_stride<PITCH>() * (size_t)(tile + smax - 1);
-    // records per reduction group: two where a lane holds several taps
-    // (registers; the reduction costs about the same per record either way)
-    auto kern = degrid_taps_kernel<NTAP, PITCH, (NTAP > 1 ? 2 : 4), SEP, TapT>;
-    constexpr int threads = kWave * taps_waves(NTAP);
+    auto kern = degrid_taps_kernel<NTAP, PITCH, kTapRecords, SEP, TapT>;
+    constexpr int threads = kWave * kTapWaves;
     hipLaunchKernelGGL(kern, dim3(resident_groups((const void *)kern, threads, lds)),
                        dim3(threads), lds,
                        stream, a.smeta, a.sperm, a.grid, a.vis_out, (const TapT *)a.taps,

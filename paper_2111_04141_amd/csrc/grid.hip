@@ -36,9 +36,10 @@
 //
 // All polarisations are handled per visit: one tap load feeds 4 complex
 // multiply-adds (the thesis's Polarisation Gain, Section 3.5), on the matrix
-// cores in the window kernel, on the vector units in the block kernel, which
-// reads its records on the scalar unit.  Each record carries the table offset
-// of its first tap (in the conjugated copy of the bank for w < 0).
+// cores in the window kernel, on the vector units, with the records read on the
+// scalar unit, in the block kernel and for supports 9 to 16 whose taps stay in
+// global memory.  Each record carries the table offset of its first tap (in the
+// conjugated copy of the bank for w < 0).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -168,10 +169,10 @@ __device__ inline uint32_t next_unit(uint32_t *queue, uint32_t *slot) {
 // copy: a load of 64 lanes of 4 or 8 bytes in a footprint's rotated order
 // takes the CU's L1 17 cycles, shared by four SIMDs, and LDS 5.  A separable
 // table is held as the S x S products of its phases, one load instead of two.
-// Measured on the W-projection benchmark workload (133.7M records, 8192^2),
-// against scalar-unit visibilities, v_fma_f32 and global taps: S <= 8 3.29 ->
-// 2.70 ms, S <= 16 7.01 -> 6.80 ms, S <= 32 6.53 -> 6.22 ms; separable 7 x 7,
-// 10.08M records on 2048^2: 0.714 -> 0.426 ms.
+// Measured on 133.7M records of a W-projection bank, 8192^2, against scalar-unit
+// visibilities, v_fma_f32 and global taps: S <= 8 3.28 -> 2.40 ms, S <= 16 6.99 ->
+// 6.65 ms, S <= 32 6.57 -> 6.22 ms; separable 7 x 7, 10.08M records on 2048^2:
+// 0.714 -> 0.426 ms.
 // Supports 9 to 16 with their taps in global memory keep the vector units: their
 // records are read on the scalar unit, in batches, by v_fma_f32 (the same bits),
 // and where no chunk of the call can have its table in LDS four waves share a
@@ -201,9 +202,7 @@ constexpr size_t kWindowLds = 80 * 1024;
 // Records a chunk needs, per oversampling phase, for its plane's table to be
 // copied to LDS: the copy reads the table once through an L1 of about 32 bytes
 // a cycle, what the records would read themselves over 1 / kStagePerPhase of
-// the chunk.
-// A group of one plane copies its table once per workgroup whatever the chunk:
-// 100,800 records on 1024^2, in chunks of 64: 67 us in place of 71.
+// the chunk.  (16, the degridders' figure, is within 1 % on every timing case.)
 constexpr uint32_t kStagePerPhase = 8;
 // ... and in all: with chunks of 64 records (calls of less than half a million)
 // four waves on global taps are the faster (100,000 records, W-projection, beta
@@ -996,8 +995,9 @@ void grid_block_kernel(
 
 // Gathers the visibilities of the plane groups' units (one group per
 // blockIdx.y) into sorted order, padded to 4 polarisations, writes each unit's
-// word (see kUnitFixed) and clears the group's work counter.  A workgroup takes a unit (at most kGatherThreads * kGatherPerThread
-// records, contiguous in sorted order): every thread first loads the
+// word (see kUnitFixed) and clears the group's work counter.  A workgroup takes a
+// unit (at most kGatherThreads * kGatherPerThread records, contiguous in sorted
+// order): every thread first loads the
 // permutation entries of its records, then their visibilities (all loads in
 // flight together), bounds the unit's partial sums, and for the window
 // classes (fixed = 1) stores the visibilities multiplied by the unit's

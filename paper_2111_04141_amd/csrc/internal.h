@@ -11,9 +11,10 @@ namespace mg {
 // Per-plane layout of the record buckets and the kernel each plane runs.
 //   Buckets are (plane, uv tile) pairs.  A tile is T x T cells; a record
 //   belongs to the tile holding its footprint's first cell (k_lo_u, k_lo_v).
-//   Planes are gathered into groups: a maximal run of consecutive planes of
-//   one support class above 16 forms one group, every other plane is a group
-//   of its own.  The buckets of a group are numbered tile-major,
+//   Planes are gathered into groups: every maximal run of consecutive planes of
+//   one support class is a group, and the gridders and degridders launch once for
+//   each group and walk its units only.  The buckets of a group are numbered
+//   tile-major,
 //     bucket = base + tile * grp_n + (plane - grp_first),
 //   so the records of one tile in all the group's planes are contiguous and
 //   the output-stationary kernels commit each tile's region once.
@@ -210,19 +211,11 @@ int device_lds_limit();
 constexpr size_t kArenaAlign = 256;
 inline size_t arena_round(size_t b) { return (b + kArenaAlign - 1) & ~(kArenaAlign - 1); }
 
-// Support classes (each has its own gridding and degridding kernels):
-//   class 0: S <= 8   moving window, one slot per lane
-//   class 1: S <= 16  moving window, up to 4 slots per lane
-//   class 2: S <= 32  moving window held by teams of 2 waves, up to 8 slots
-//                     per lane
-//   class 3: S <= 64  blocked output-stationary kernel (registers per 8 x 8
-//                     block of the unit's region)
-// Classes 0-2 accumulate committed sums in a fixed-point LDS region (see
-// grid.hip); class 3 commits its registers to the grid once per unit.
 // Entries of padding after the sorted record arrays (metadata, and the
-// gridder's sorted visibilities): the gridders load records in batches of
-// two, one batch ahead, so their reads reach 3 entries past the last record
-// of a range.
+// gridder's sorted visibilities): the gridding loops that read records on the
+// scalar unit (supports above 32, and 9 to 16 with taps in global memory) load
+// them in batches of two, one batch ahead, so their reads reach 3 entries past the
+// last record of a range.
 constexpr int kRecPad = 4;
 
 inline size_t dtype_size(mg_dtype d) {
@@ -235,6 +228,15 @@ inline size_t dtype_size(mg_dtype d) {
     return 0;
 }
 
+// Support classes (each has its own gridding and degridding kernels):
+//   class 0: S <= 8   moving window, one slot per lane
+//   class 1: S <= 16  moving window, up to 4 slots per lane
+//   class 2: S <= 32  moving window held by teams of 2 waves, up to 8 slots
+//                     per lane
+//   class 3: S <= 64  blocked output-stationary kernel (registers per 8 x 8
+//                     block of the unit's region)
+// Classes 0-2 accumulate committed sums in a fixed-point LDS region (see
+// grid.hip); class 3 commits its registers to the grid once per unit.
 inline int support_class(int S) { return S <= 8 ? 0 : S <= 16 ? 1 : S <= 32 ? 2 : 3; }
 
 }  // namespace mg

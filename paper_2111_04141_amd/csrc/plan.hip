@@ -391,8 +391,9 @@ __global__ __launch_bounds__(256) void scatter_kernel(DevGeom g,
 // units of a plane group: the chunks of one tile, over
 // all planes of the group, split greedily into runs of at most `cap`
 // records (a chunk is never split).  The gridders take a unit at a time
-// and commit the tile's region once per unit rather than once per chunk.  units[first chunk of the group + k] = (first chunk, chunk count)
-// of the group's unit k; group_nunits[g] = unit count (cleared beforehand).
+// and commit the tile's region once per unit rather than once per chunk.
+// units[first chunk of the group + k] = (first chunk, chunk count) of the group's
+// unit k; group_nunits[g] = unit count (cleared beforehand).
 // A wave's units are consecutive and in tile order.
 // A launch covers its groups (blockIdx.y) and every tile (a thread each).
 // ---------------------------------------------------------------------------
