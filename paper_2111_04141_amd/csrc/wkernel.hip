@@ -54,8 +54,8 @@ namespace {
 
 // The planes of a bank (kernel argument).  The workspace of plane p, in
 // doubles from ws[p]: cos table [M], taper [H + 1], padded to even, then
-// complex X [H + 1][H + 1], B [H + 1][h + 1], K [h + 1][h + 1], H = M/2 = beta
-// S, h = H/2; H above kCosineMax: X [M][M] (its transform takes its place), K.
+// complex K [h + 1][h + 1], X [H + 1][H + 1], B [H + 1][h + 1], H = M/2 = beta
+// S, h = H/2; H above kCosineMax: K, X [M][M] (its transform takes its place).
 struct BankPlanes {
     int64_t ws[kMaxPlanes];
     int64_t bank[kMaxPlanes];   // complex elements into the bank
@@ -88,14 +88,9 @@ __device__ inline PlaneWork plane_work(const BankPlanes &P, int p, int beta, dou
     w.h = w.H / 2;
     w.ct = ws + P.ws[p];
     w.taper = w.ct + w.M;
-    w.X = reinterpret_cast<double2 *>(w.ct + table_doubles(w.H));
-    if (w.H > kCosineMax) {
-        w.B = nullptr;
-        w.K = w.X + (int64_t)w.M * w.M;
-        return w;
-    }
+    w.K = reinterpret_cast<double2 *>(w.ct + table_doubles(w.H));
+    w.X = w.K + (int64_t)(w.h + 1) * (w.h + 1);
     w.B = w.X + (int64_t)(w.H + 1) * (w.H + 1);
-    w.K = w.B + (int64_t)(w.H + 1) * (w.h + 1);
     return w;
 }
 
@@ -122,17 +117,20 @@ __global__ __launch_bounds__(256) void tables_kernel(BankPlanes P, int32_t beta,
     }
 }
 
-__global__ __launch_bounds__(256) void screen_kernel(BankPlanes P, int32_t beta, double fov,
-                                                     double *__restrict__ ws) {
-    const PlaneWork w = plane_work(P, blockIdx.y, beta, ws);
-    // the quadrant, weighted; or the whole image in transform order
-    const bool full = w.H > kCosineMax;
-    const int side = full ? w.M : w.H + 1;
-    const double wp = P.w[blockIdx.y];
+// The weighted quadrant of every plane up to kCosineMax; FULL: the whole image of
+// plane `plane`, in transform order.
+template <bool FULL>
+__global__ __launch_bounds__(256) void screen_kernel(BankPlanes P, int32_t plane, int32_t beta,
+                                                     double fov, double *__restrict__ ws) {
+    const int p = FULL ? plane : (int)blockIdx.y;
+    const PlaneWork w = plane_work(P, p, beta, ws);
+    if (!FULL && w.H > kCosineMax) return;
+    const int side = FULL ? w.M : w.H + 1;
+    const double wp = P.w[p];
     for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < side * side;
          k += gridDim.x * blockDim.x) {
         int i = k / side, j = k - i * side;
-        if (full) {   // (even along both axes)
+        if constexpr (FULL) {   // (even along both axes)
             i = min(i, w.M - i);
             j = min(j, w.M - j);
         }
@@ -143,7 +141,7 @@ __global__ __launch_bounds__(256) void screen_kernel(BankPlanes P, int32_t beta,
         double sn, cs;
         sincospi(2.0 * (wp * (nn - 1.0)), &sn, &cs);
         double e = 1.0;
-        if (!full) e = (i == 0 || i == w.H ? 1.0 : 2.0) * (j == 0 || j == w.H ? 1.0 : 2.0);
+        if constexpr (!FULL) e = (i == 0 || i == w.H ? 1.0 : 2.0) * (j == 0 || j == w.H ? 1.0 : 2.0);
         const double a = e * w.taper[i] * w.taper[j];
         w.X[k] = make_double2(a * cs, a * sn);
     }
@@ -358,8 +356,8 @@ hipfftResult bank_fft(int dev, int M, BankFft *out) {
     return HIPFFT_SUCCESS;
 }
 
-// Transforms and quadrants of the planes above kCosineMax.
-mg_status large_planes(const Layout &L, int32_t nplanes, int32_t beta, double *ws,
+// Images, transforms and quadrants of the planes above kCosineMax.
+mg_status large_planes(const Layout &L, int32_t nplanes, int32_t beta, double fov, double *ws,
                        unsigned long long *mx, hipStream_t stream) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return set_error(MG_EDEVICE, "no device");
@@ -387,8 +385,11 @@ mg_status large_planes(const Layout &L, int32_t nplanes, int32_t beta, double *w
     for (int p = 0; p < nplanes && r == HIPFFT_SUCCESS; ++p) {
         const int H = beta * (int)L.planes.S[p];
         if (H <= kCosineMax) continue;
-        hipfftDoubleComplex *img =
-            reinterpret_cast<hipfftDoubleComplex *>(ws + L.planes.ws[p] + table_doubles(H));
+        const int64_t n = (int64_t)(H / 2 + 1) * (H / 2 + 1), m = 4 * (int64_t)H * H;
+        hipfftDoubleComplex *img = reinterpret_cast<hipfftDoubleComplex *>(
+            ws + L.planes.ws[p] + table_doubles(H) + 2 * n);
+        hipLaunchKernelGGL(screen_kernel<true>, dim3((unsigned)std::min<int64_t>((m + 255) / 256, 4096)),
+                           dim3(256), 0, stream, L.planes, p, beta, fov, ws);
         {
             // the plan is shared: its stream and work area are set and the
             // transform queued under the lock
@@ -399,7 +400,6 @@ mg_status large_planes(const Layout &L, int32_t nplanes, int32_t beta, double *w
             if (r == HIPFFT_SUCCESS && f.work) r = hipfftSetWorkArea(f.h, area);
             if (r == HIPFFT_SUCCESS) r = hipfftExecZ2Z(f.h, img, img, HIPFFT_FORWARD);
         }
-        const int64_t n = (int64_t)(H / 2 + 1) * (H / 2 + 1);
         if (r == HIPFFT_SUCCESS)
             hipLaunchKernelGGL(quadrant_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)),
                                dim3(256), 0, stream, L.planes, p, beta, ws, mx);
@@ -451,35 +451,38 @@ mg_status mg_wkernel_bank(int32_t nplanes, const int32_t *plane_support, const d
         reinterpret_cast<unsigned long long *>(static_cast<char *>(workspace) + L.off_max);
     // grids for the largest plane; the others' spare workgroups have nothing
     // to do
-    const int64_t side = L.H_max > kCosineMax ? 2 * L.H_max : L.H_max + 1;
     const int64_t tile_rows = (L.H_cosine + 1 + 15) / 16,
                   tile_cols = (L.H_cosine / 2 + 1 + 15) / 16;
     auto over = [&](int64_t groups) {
         return dim3((unsigned)std::max<int64_t>(1, groups), (unsigned)nplanes);
     };
-    const dim3 elems = over(std::min<int64_t>((side * side + 255) / 256, 4096));
+    auto elems = [&](int64_t side) {
+        return over(std::min<int64_t>((side * side + 255) / 256, 4096));
+    };
+    const dim3 kept = elems(L.H_max + 1);
     hipLaunchKernelGGL(tables_kernel, over((L.H_max + 1 + 3) / 4), dim3(256), 0, stream, L.planes, beta,
                        base_len, base_taps, ws, mx);
-    hipLaunchKernelGGL(screen_kernel, elems, dim3(256), 0, stream, L.planes, beta, fov, ws);
     if (L.H_cosine) {
+        hipLaunchKernelGGL(screen_kernel<false>, elems(L.H_cosine + 1), dim3(256), 0, stream,
+                           L.planes, 0, beta, fov, ws);
         hipLaunchKernelGGL(cosine_kernel<0>, over(tile_rows * tile_cols), dim3(256), 0,
                            stream, L.planes, beta, ws, mx);
         hipLaunchKernelGGL(cosine_kernel<1>, over(tile_cols * tile_cols), dim3(256), 0,
                            stream, L.planes, beta, ws, mx);
     }
     if (L.H_max > kCosineMax) {
-        st = large_planes(L, nplanes, beta, ws, mx, stream);
+        st = large_planes(L, nplanes, beta, fov, ws, mx, stream);
         if (st != MG_OK) return st;
     }
     const unsigned long long *cmx = mx;
     if (out_dtype == MG_F16)
-        hipLaunchKernelGGL(store_kernel<__half>, elems, dim3(256), 0, stream, L.planes, beta, ws,
+        hipLaunchKernelGGL(store_kernel<__half>, kept, dim3(256), 0, stream, L.planes, beta, ws,
                            cmx, (__half *)bank);
     else if (out_dtype == MG_BF16)
-        hipLaunchKernelGGL(store_kernel<__hip_bfloat16>, elems, dim3(256), 0, stream, L.planes,
+        hipLaunchKernelGGL(store_kernel<__hip_bfloat16>, kept, dim3(256), 0, stream, L.planes,
                            beta, ws, cmx, (__hip_bfloat16 *)bank);
     else
-        hipLaunchKernelGGL(store_kernel<float>, elems, dim3(256), 0, stream, L.planes, beta, ws,
+        hipLaunchKernelGGL(store_kernel<float>, kept, dim3(256), 0, stream, L.planes, beta, ws,
                            cmx, (float *)bank);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return set_error(MG_EDEVICE, std::string("kernel bank: ") + hipGetErrorString(e));
