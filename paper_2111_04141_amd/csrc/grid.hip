@@ -204,7 +204,7 @@ constexpr size_t kWindowLds = 80 * 1024;
 // a cycle, what the records would read themselves over 1 / kStagePerPhase of
 // the chunk.  (16, the degridders' figure, is within 1 % on every timing case.)
 constexpr uint32_t kStagePerPhase = 8;
-// ... and in all: with chunks of 64 records (calls of less than half a million)
+// ... and in all: with chunks of fewer records (calls of less than half a million)
 // four waves on global taps are the faster (100,000 records, W-projection, beta
 // 2, S = 16, one polarisation: 128 -> 91 us).
 constexpr uint32_t kStageLeast = 128;
